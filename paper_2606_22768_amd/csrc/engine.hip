@@ -166,8 +166,9 @@ fgd_status ensure_topology(fgd_engine *e, hipStream_t stream, int &ring) {
         return FGD_OK;
     }
     std::vector<int32_t> t1, t2;
-    e->slot[0].pack_tables(t1);
-    e->slot[1].pack_tables(t2);
+    const int32_t stride = fgd::worker_class(e->cfg.num_workers);  // the kernels' table rows
+    e->slot[0].pack_tables(t1, stride);
+    e->slot[1].pack_tables(t2, stride);
     const size_t b1 = t1.size() * sizeof(int32_t), b2 = t2.size() * sizeof(int32_t);
     const size_t so = subset_offset(b1 + b2), bs = e->subset.size() * sizeof(int64_t);
     if (so + bs > e->topo_capacity) return fail(FGD_ERR_UNSUPPORTED, "topology tables exceed the device slot");
@@ -198,7 +199,8 @@ fgd_status ensure_topology(fgd_engine *e, hipStream_t stream, int &ring) {
 // inside a ring slot.
 void table_ptrs(const fgd_engine *e, int ring, const void *&t1, const void *&t2, const int64_t *&seg) {
     auto bytes = [&](const fgd::MixTopology &t) {
-        return static_cast<size_t>(t.kind == 2 ? t.rounds * t.width : 0) * e->cfg.num_workers * 2 * sizeof(int32_t);
+        return static_cast<size_t>(t.kind == 2 ? t.rounds * t.width : 0) * fgd::worker_class(e->cfg.num_workers) * 2 *
+               sizeof(int32_t);
     };
     const size_t b1 = bytes(e->slot[0]), b2 = bytes(e->slot[1]);
     t1 = e->d_topo[ring];
@@ -503,7 +505,8 @@ fgd_status fgd_create(const fgd_config *cfg, fgd_engine **out) {
         const size_t M = static_cast<size_t>(cfg->num_workers);
         // Largest packed tables (both slots, FGD_MAX_ROUNDS rounds, width M),
         // then the largest subset.
-        e->topo_capacity = subset_offset(2 * static_cast<size_t>(FGD_MAX_ROUNDS) * M * M * 2 * sizeof(int32_t)) +
+        e->topo_capacity = subset_offset(2 * static_cast<size_t>(FGD_MAX_ROUNDS) * M *
+                                         fgd::worker_class(cfg->num_workers) * 2 * sizeof(int32_t)) +
                            static_cast<size_t>(FGD_MAX_SUBSET_SEGMENTS) * 2 * sizeof(int64_t);
         const int n_cd_max = 2 * FGD_MAX_ROUNDS + 3;
         e->partials_capacity = static_cast<size_t>(e->num_cus) * kMaxBlocksPerCu * n_cd_max * M;
@@ -728,7 +731,7 @@ fgd_status fgd_outer_step(fgd_engine *e, void *theta_prev, const void *theta_loc
     const bool padded = (e->slot[0].kind == 2 && e->slot[0].padded) || (e->slot[1].kind == 2 && e->slot[1].padded);
     p.lds_rows = tables ? c.num_workers + (padded ? 1 : 0) : 0;
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
-    if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.mmax * sizeof(double);
+    if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
 
     // 64 workers on sparse tables: the worker-group kernel.
     fgd::WgKernel wk{};
@@ -864,7 +867,7 @@ fgd_status fgd_mix1(fgd_engine *e, const void *theta_prev, void *x_out, float *m
     p.n_cd = e->slot[0].effective_rounds() + 1;
     p.lds_rows = lds_rows_for(e, true, false);
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
-    if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.mmax * sizeof(double);
+    if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
     int grid = 0;
     if (fgd_status st = grid_for(e, ks.mix1, lds, p.ntiles, grid, ks.blocks_per_cu)) return st;
     if (num_blocks > 0) grid = std::min(grid, num_blocks);
@@ -923,7 +926,7 @@ fgd_status fgd_outer_step_blocking(fgd_engine *e, const void *x, void *theta_pre
     p.n_cd = e->slot[1].effective_rounds() + 2;
     p.lds_rows = lds_rows_for(e, false, true);
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
-    if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.mmax * sizeof(double);
+    if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
     int grid = 0;
     if (fgd_status st = grid_for(e, ks.blocking, lds, p.ntiles, grid, ks.blocks_per_cu)) return st;
     if (cd_out) {

@@ -100,6 +100,31 @@ struct ConsensusParams {
 constexpr int pow2_at_least(int m) { return m <= 1 ? 1 : 2 * pow2_at_least((m + 1) / 2); }
 constexpr int ilog2(int m) { return m <= 1 ? 0 : 1 + ilog2(m / 2); }
 
+// Worker classes.  M in {1, 2, 4, 8, 16, 32, 64} has kernels of its own
+// (EXACT).  Every other M runs on the kernels of the smallest class bound
+// MMAX >= M below, with M read at run time: their rows m >= M take part in
+// every instruction, but their descriptors have a record count of 0, so
+// their loads return 0 and their stores write nothing, neither moving a byte
+// nor branching.  (With a branch around each row's load the loads of a tile
+// are not issued together, and the next power of two has up to half its rows
+// dead: the step at 12 workers x 7M bf16 took 596 us so and 303 with classes,
+// at 24 workers 1257 and 693 us; the consensus of 24 x 40M bf16 857 and 384.)
+// The classes are close together, so that at most a fifth of the rows is
+// dead from 9 workers on.
+constexpr int worker_class(int m) {
+    return m <= 2 ? m
+           : m <= 16 ? (m + 1) / 2 * 2
+           : m <= 32 ? (m + 3) / 4 * 4
+                     : (m + 7) / 8 * 8;
+}
+// The smallest M of class `mmax`: rows below it need no run-time check.
+constexpr int class_floor(int mmax) { return mmax <= 2 ? mmax : (mmax <= 16 ? mmax - 1 : (mmax <= 32 ? mmax - 3 : mmax - 7)); }
+// Whether row m exists (a constant for every row but the last few of a class).
+template <int MMAX, bool EXACT>
+__host__ __device__ constexpr bool row_live(int m, int M) {
+    return EXACT || m < class_floor(MMAX) || m < M;
+}
+
 // ------------------------------------------------------------ tuning knobs
 // Defaults are the shipped configuration; variants are built with -D.
 
@@ -134,6 +159,11 @@ constexpr int kRawBufferFlags = 0x00020000;   // raw (untyped) buffer descriptor
 __device__ __forceinline__ rsrc_t row_rsrc(const void *base, int64_t elem, int es) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(base)) + elem * es,
                                              static_cast<short>(0), 0x7fffffff, kRawBufferFlags);
+}
+// The same for a row that may not exist: its accesses read 0 and write nothing.
+__device__ __forceinline__ rsrc_t row_rsrc_if(bool live, const void *base, int64_t elem, int es) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(base)) + elem * es,
+                                             static_cast<short>(0), live ? 0x7fffffff : 0, kRawBufferFlags);
 }
 
 // float32 values, V in {1, 2, 4}; `off` is the lane's byte offset in the row.
@@ -340,7 +370,7 @@ __device__ inline float wave_reduce_scatter(float (&part)[C], int lane) {
 template <int MMAX, bool EXACT, int V, int LO, int N>
 __device__ __forceinline__ float tree_sum(const float (&u)[MMAX][V], int M, int v) {
     if constexpr (N == 1) {
-        return (EXACT || LO < M) ? u[LO][v] : 0.0f;
+        return row_live<MMAX, EXACT>(LO, M) ? u[LO][v] : 0.0f;
     } else {
         return tree_sum<MMAX, EXACT, V, LO, N / 2>(u, M, v) + tree_sum<MMAX, EXACT, V, LO + N / 2, N - N / 2>(u, M, v);
     }
@@ -363,13 +393,13 @@ __device__ inline void cd_accumulate_about(const float (&u)[MMAX][V], const floa
     constexpr int C = MP < 16 ? MP : 16;
     constexpr int kShift = 6 - ilog2(C);
 #pragma unroll
-    for (int c = 0; c < MP / C; ++c) {
+    for (int c = 0; c < (MMAX + C - 1) / C; ++c) {
         float part[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const int m = c * C + j;
             float t = 0.0f;
-            if (m < MMAX && (EXACT || m < M)) {
+            if (m < MMAX) {  // a row that does not exist leaves its sum in no accumulator
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
                     const float d = u[m < MMAX ? m : 0][v] - mean[v];
@@ -434,10 +464,10 @@ constexpr int kWideTable = 16;
 template <int MMAX, bool EXACT, int V>
 __device__ inline void table_round_lds(const_table_ptr tab, int width, int M, float (&u)[MMAX][V], float *rows,
                                        int tid) {
-    const int Mr = EXACT ? MMAX : M;
+    constexpr int Mr = MMAX;  // the tables' entries for rows that do not exist are (0, 0)
 #pragma unroll
     for (int m = 0; m < MMAX; ++m) {
-        if (EXACT || m < M) {
+        if (row_live<MMAX, EXACT>(m, M)) {
             float *dst = rows + (static_cast<int64_t>(m) * kBlock + tid) * V;
             if constexpr (V == 4) {
                 *reinterpret_cast<f32x4 *>(dst) = f32x4{u[m][0], u[m][1], u[m][2], u[m][3]};
@@ -461,7 +491,7 @@ __device__ inline void table_round_lds(const_table_ptr tab, int width, int M, fl
 #pragma unroll
             for (int m = 0; m < MMAX; ++m) {
                 if (m % 8 == 0 && m > 0) __builtin_amdgcn_sched_barrier(0);
-                if (EXACT || m < M) {
+                {
                     float r0[V], r1[V], r2[V], r3[V];
                     lds_row<V>(rows, td[2 * m], tid, r0);
                     lds_row<V>(rows, td[2 * Mr + 2 * m], tid, r1);
@@ -486,7 +516,7 @@ __device__ inline void table_round_lds(const_table_ptr tab, int width, int M, fl
             // Keep the scheduler from hoisting every row's table entry into
             // scalar registers at once.
             if (m % 16 == 0 && m > 0) __builtin_amdgcn_sched_barrier(0);
-            if (EXACT || m < M) {
+            {
                 const float w = __int_as_float(td[2 * m + 1]);
                 float r[V];
                 lds_row<V>(rows, td[2 * m], tid, r);
@@ -517,7 +547,7 @@ template <int MMAX, bool EXACT, int V>
 __device__ inline void keep_own(float (&u)[MMAX][V], const float *rows, int tid, int M, uint32_t keep) {
 #pragma unroll
     for (int m = 0; m < MMAX; ++m) {
-        if (EXACT || m < M) {
+        if (row_live<MMAX, EXACT>(m, M)) {
             const float *own = rows + (static_cast<int64_t>(m) * kBlock + tid) * V;
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -562,9 +592,8 @@ __device__ inline void mix_apply(const MixDev &mx, int M, float (&u)[MMAX][V], c
             return;
         }
         if (KIND == kAny && mx.kind != kTable) return;
-        const int Mr = EXACT ? MMAX : M;
         for (int k = 0; k < mx.rounds; ++k) {
-            const_table_ptr tab = (const_table_ptr)(mx.table) + 2 * static_cast<int64_t>(k) * mx.width * Mr;
+            const_table_ptr tab = (const_table_ptr)(mx.table) + 2 * static_cast<int64_t>(k) * mx.width * MMAX;
             table_round<MMAX, EXACT, V>(tab, mx.width, M, u, rows, tid);
             if (keep) keep_own<MMAX, EXACT, V>(u, rows, tid, M, keep);
             if (cd_acc) cd_accumulate_about<MMAX, EXACT, V>(u, mean, M, cd_acc + k * cd_stride, lane);
@@ -613,17 +642,16 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
     if (FULL || nv > 0) {
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {
-            if (EXACT || m < M) {
-                PIO::load(row_rsrc(a.theta_prev, m * a.ld + tb, kE), off_p, u1[m]);
-                PIO::load(row_rsrc(a.theta_local, m * a.ld + tb, kE), off_p, u2[m]);
-            }
+            const bool live = row_live<MMAX, EXACT>(m, M);
+            PIO::load(row_rsrc_if(live, a.theta_prev, m * a.ld + tb, kE), off_p, u1[m]);
+            PIO::load(row_rsrc_if(live, a.theta_local, m * a.ld + tb, kE), off_p, u2[m]);
         }
     }
 #pragma unroll
     for (int m = 0; m < MMAX; ++m) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            if ((EXACT || m < M) && (FULL || v < nv)) u2[m][v] = u1[m][v] - u2[m][v];
+            if (FULL || v < nv) u2[m][v] = u1[m][v] - u2[m][v];
             else { u1[m][v] = 0.0f; u2[m][v] = 0.0f; }
         }
     }
@@ -657,7 +685,8 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
     // xs: the row's stored x (kStored only).
     auto finish_row = [&](int m, float (&vr)[V], const float (&xs)[V]) {
         float stored[V];
-        if ((EXACT || m < M) && (FULL || nv > 0)) {
+        if (FULL || nv > 0) {
+            const bool live = row_live<MMAX, EXACT>(m, M);
             float t[V];
 #pragma unroll
             for (int e = 0; e < V; ++e) {
@@ -667,8 +696,8 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
                 const float step = nesterov ? fmaf(mu, vr[e], g) : vr[e];
                 t[e] = fmaf(-lr, step, x);
             }
-            const rsrc_t rv = row_rsrc(a.mom_out, m * a.ld + tb, 4);
-            const rsrc_t rp = row_rsrc(a.theta_out, m * a.ld + tb, kE);
+            const rsrc_t rv = row_rsrc_if(live, a.mom_out, m * a.ld + tb, 4);
+            const rsrc_t rp = row_rsrc_if(live, a.theta_out, m * a.ld + tb, kE);
             if (FULL || nv == V) {
                 F32Io<V>::store(rv, off_v, vr);
                 PIO::store(rp, off_p, t, stored);
@@ -679,7 +708,7 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
             if constexpr (K1 == kStored) {
                 if (a.local_out) {  // theta' (already in storage precision) as the next inner start
                     float again[V];
-                    const rsrc_t rl = row_rsrc(a.local_out, m * a.ld + tb, kE);
+                    const rsrc_t rl = row_rsrc_if(live, a.local_out, m * a.ld + tb, kE);
                     if (FULL || nv == V) PIO::store(rl, off_p, stored, again);
                     else PIO::store_part(rl, off_p, nv, stored, again);
                 }
@@ -701,7 +730,8 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
         float vm[MMAX][V];
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {
-            if ((EXACT || m < M) && (FULL || nv > 0)) F32Io<V>::load(row_rsrc(a.mom, m * a.ld + tb, 4), off_v, vm[m]);
+            if (FULL || nv > 0)
+                F32Io<V>::load(row_rsrc_if(row_live<MMAX, EXACT>(m, M), a.mom, m * a.ld + tb, 4), off_v, vm[m]);
             else {
 #pragma unroll
                 for (int e = 0; e < V; ++e) vm[m][e] = 0.0f;
@@ -731,9 +761,10 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
 #pragma unroll
                 for (int j = 0; j < G; ++j) {
                     const int m = m0 + j;
-                    if (m < MMAX && (EXACT || m < M)) {
-                        F32Io<V>::load(row_rsrc(a.mom, m * a.ld + tb, 4), off_v, vm[j]);
-                        if constexpr (K1 == kStored) PIO::load(row_rsrc(a.x, m * a.ld + tb, kE), off_p, xm[j]);
+                    if (m < MMAX) {
+                        const bool live = row_live<MMAX, EXACT>(m, M);
+                        F32Io<V>::load(row_rsrc_if(live, a.mom, m * a.ld + tb, 4), off_v, vm[j]);
+                        if constexpr (K1 == kStored) PIO::load(row_rsrc_if(live, a.x, m * a.ld + tb, kE), off_p, xm[j]);
                     }
                 }
             }
@@ -869,13 +900,13 @@ __device__ __forceinline__ void mix1_tile(const StepParams &a, const TileCtx &c,
     if (FULL || nv > 0) {
 #pragma unroll
         for (int m = 0; m < MMAX; ++m)
-            if (EXACT || m < M) PIO::load(row_rsrc(a.theta_prev, m * a.ld + tb, kE), off_p, u[m]);
+            PIO::load(row_rsrc_if(row_live<MMAX, EXACT>(m, M), a.theta_prev, m * a.ld + tb, kE), off_p, u[m]);
     }
 #pragma unroll
     for (int m = 0; m < MMAX; ++m)
 #pragma unroll
         for (int v = 0; v < V; ++v)
-            if (!((EXACT || m < M) && (FULL || v < nv))) u[m][v] = 0.0f;
+            if (!(FULL || v < nv)) u[m][v] = 0.0f;
     float xbar[V];
     row_mean<MMAX, EXACT, V>(u, M, xbar);
     if (c.cd_acc) cd_accumulate_about<MMAX, EXACT, V>(u, xbar, M, c.cd_acc, c.lane);
@@ -884,9 +915,9 @@ __device__ __forceinline__ void mix1_tile(const StepParams &a, const TileCtx &c,
     if (FULL || nv > 0) {
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {
-            if (EXACT || m < M) {
+            {
                 float stored[V];
-                const rsrc_t rx = row_rsrc(a.x_out, m * a.ld + tb, kE);
+                const rsrc_t rx = row_rsrc_if(row_live<MMAX, EXACT>(m, M), a.x_out, m * a.ld + tb, kE);
                 if (FULL || nv == V) PIO::store(rx, off_p, K1 == kGlobal ? xbar : u[m], stored);
                 else PIO::store_part(rx, off_p, nv, K1 == kGlobal ? xbar : u[m], stored);
             }
@@ -896,7 +927,8 @@ __device__ __forceinline__ void mix1_tile(const StepParams &a, const TileCtx &c,
         float vm[MMAX][V];
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {
-            if ((EXACT || m < M) && (FULL || nv > 0)) F32Io<V>::load(row_rsrc(a.mom, m * a.ld + tb, 4), off_v, vm[m]);
+            if (FULL || nv > 0)
+                F32Io<V>::load(row_rsrc_if(row_live<MMAX, EXACT>(m, M), a.mom, m * a.ld + tb, 4), off_v, vm[m]);
             else {
 #pragma unroll
                 for (int e = 0; e < V; ++e) vm[m][e] = 0.0f;
@@ -908,8 +940,8 @@ __device__ __forceinline__ void mix1_tile(const StepParams &a, const TileCtx &c,
         if (FULL || nv > 0) {
 #pragma unroll
             for (int m = 0; m < MMAX; ++m) {
-                if (EXACT || m < M) {
-                    const rsrc_t rv = row_rsrc(a.mom_out, m * a.ld + tb, 4);
+                {
+                    const rsrc_t rv = row_rsrc_if(row_live<MMAX, EXACT>(m, M), a.mom_out, m * a.ld + tb, 4);
                     if (FULL || nv == V) F32Io<V>::store(rv, off_v, K1 == kGlobal ? vbar : vm[m]);
                     else F32Io<V>::store_part(rv, off_v, nv, K1 == kGlobal ? vbar : vm[m]);
                 }
@@ -1003,13 +1035,13 @@ __global__ __launch_bounds__(kBlock) void consensus_kernel(ConsensusParams a) {
         if (nv > 0) {
 #pragma unroll
             for (int m = 0; m < MMAX; ++m)
-                if (EXACT || m < M) PIO::load(row_rsrc(a.x, m * a.ld + tb, kE), lo * kE, u[m]);
+                PIO::load(row_rsrc_if(row_live<MMAX, EXACT>(m, M), a.x, m * a.ld + tb, kE), lo * kE, u[m]);
         }
 #pragma unroll
         for (int m = 0; m < MMAX; ++m)
 #pragma unroll
             for (int v = 0; v < V; ++v)
-                if (!((EXACT || m < M) && v < nv)) u[m][v] = 0.0f;
+                if (!(v < nv)) u[m][v] = 0.0f;
         cd_accumulate<MMAX, EXACT, V>(u, M, acc + wave * MP, lane);
     }
     __syncthreads();
@@ -1130,7 +1162,7 @@ struct KernelSet {
     const void *step;       // outer_step_kernel instantiation for the requested kinds
     const void *consensus;  // consensus_kernel instantiation
     int v;                  // elements per lane per row
-    int mmax;               // compile-time worker bound
+    int cd_stride;          // consensus accumulators per wave and row (doubles)
     int step_blocks_per_cu; // cap on resident step blocks per compute unit
 };
 
@@ -1156,7 +1188,12 @@ KernelSet make_kernel_set(int k1, int k2, bool subset) {
     using P = PIOT<V>;
     KernelSet ks;
     ks.step = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kAny, kAny, kSubset>);
-    if constexpr (EXACT) {
+    if constexpr (!EXACT) {
+        if (!subset && k1 == kGlobal && k2 == kTable)
+            ks.step = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kGlobal, kTable, 0>);
+        else if (!subset && k1 == kTable && k2 == kTable)
+            ks.step = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kTable, kTable, 0>);
+    } else {
         if (subset) {
             if (k1 == kGlobal && k2 == kTable)
                 ks.step = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kGlobal, kTable, kSubset>);
@@ -1172,7 +1209,7 @@ KernelSet make_kernel_set(int k1, int k2, bool subset) {
     }
     ks.consensus = reinterpret_cast<const void *>(&consensus_kernel<MMAX, EXACT, V, P>);
     ks.v = V;
-    ks.mmax = MMAX;
+    ks.cd_stride = pow2_at_least(MMAX);
     ks.step_blocks_per_cu = step_blocks_per_cu(MMAX);
     return ks;
 }
@@ -1196,7 +1233,7 @@ KernelSet make_kernel_set_ms(int k1, int k2, bool subset) {
     }
     ks.consensus = reinterpret_cast<const void *>(&consensus_kernel<MMAX, EXACT, V, P>);
     ks.v = V;
-    ks.mmax = MMAX;
+    ks.cd_stride = pow2_at_least(MMAX);
     // With both the state mix and a subset the kernel's per-tile work no
     // longer hides behind one block's loads: at 8 workers x 1.1e9 bf16 it
     // took 22.9 ms with one block per CU and 21.6 ms with two (the other
@@ -1212,7 +1249,7 @@ struct SplitSet {
     const void *mix1;
     const void *blocking;
     int v;
-    int mmax;
+    int cd_stride;
     int blocks_per_cu;
 };
 
@@ -1223,17 +1260,18 @@ SplitSet make_split_set(int k1, int k2, bool subset, bool mix_state) {
     ks.mix1 = mix_state ? reinterpret_cast<const void *>(&mix1_kernel<MMAX, EXACT, V, P, kAny, true>)
                         : reinterpret_cast<const void *>(&mix1_kernel<MMAX, EXACT, V, P, kAny, false>);
     ks.blocking = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kStored, kAny, kSubset>);
+    if (k1 == kGlobal && !mix_state)
+        ks.mix1 = reinterpret_cast<const void *>(&mix1_kernel<MMAX, EXACT, V, P, kGlobal, false>);
+    if (k2 == kTable && !subset)
+        ks.blocking = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kStored, kTable, 0>);
     if constexpr (EXACT) {
-        if (k1 == kGlobal)
-            ks.mix1 = mix_state ? reinterpret_cast<const void *>(&mix1_kernel<MMAX, EXACT, V, P, kGlobal, true>)
-                                : reinterpret_cast<const void *>(&mix1_kernel<MMAX, EXACT, V, P, kGlobal, false>);
-        if (k2 == kTable)
-            ks.blocking = subset ? reinterpret_cast<const void *>(
-                                       &outer_step_kernel<MMAX, EXACT, V, P, kStored, kTable, kSubset>)
-                                 : reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kStored, kTable, 0>);
+        if (k1 == kGlobal && mix_state)
+            ks.mix1 = reinterpret_cast<const void *>(&mix1_kernel<MMAX, EXACT, V, P, kGlobal, true>);
+        if (k2 == kTable && subset)
+            ks.blocking = reinterpret_cast<const void *>(&outer_step_kernel<MMAX, EXACT, V, P, kStored, kTable, kSubset>);
     }
     ks.v = V;
-    ks.mmax = MMAX;
+    ks.cd_stride = pow2_at_least(MMAX);
     ks.blocks_per_cu = step_blocks_per_cu(MMAX);
     return ks;
 }
@@ -1241,30 +1279,49 @@ SplitSet make_split_set(int k1, int k2, bool subset, bool mix_state) {
 // Elements per lane per row: 16-byte float32 accesses up to 8 workers; bf16
 // parameters use 8-byte accesses (4 elements) so that momentum still moves in
 // 16-byte accesses and the register and LDS footprint per lane stays small.
-constexpr int lanes_v_f32(int mmax) { return mmax <= 8 ? 4 : (mmax == 16 ? FGD_V_F32_M16 : (mmax == 32 ? 2 : 1)); }
+constexpr int lanes_v_f32(int mmax) { return mmax <= 8 ? 4 : (mmax <= 16 ? FGD_V_F32_M16 : (mmax <= 32 ? 2 : 1)); }
 constexpr int lanes_v_bf16(int mmax) {
-    return mmax <= 8 ? FGD_V_BF16_M8 : (mmax == 16 ? 4 : (mmax == 32 ? 2 : 1));
+    return mmax <= 8 ? FGD_V_BF16_M8 : (mmax <= 16 ? 4 : (mmax <= 32 ? 2 : 1));
 }
 
 // Calls F::get<MMAX, EXACT>(args...) for the instantiation that serves M
-// workers: exact for M in {1, 2, 4, 8, 16, 32, 64}, else the next power of
-// two with M read at run time.
+// workers: select_exact for M in {1, 2, 4, 8, 16, 32, 64}, select_class for
+// every other M up to 63 (see worker_class).
+constexpr bool exact_workers(int M) { return M >= 1 && M <= 64 && (M & (M - 1)) == 0; }
 template <class F, class Out, class... A>
-bool select_workers(int M, Out *out, A... args) {
+bool select_exact(int M, Out *out, A... args) {
+    switch (M) {
+        case 1: *out = F::template get<1, true>(args...); return true;
+        case 2: *out = F::template get<2, true>(args...); return true;
+        case 4: *out = F::template get<4, true>(args...); return true;
+        case 8: *out = F::template get<8, true>(args...); return true;
+        case 16: *out = F::template get<16, true>(args...); return true;
+        case 32: *out = F::template get<32, true>(args...); return true;
+        case 64: *out = F::template get<64, true>(args...); return true;
+        default: return false;
+    }
+}
+template <class F, class Out, class... A>
+bool select_class(int M, Out *out, A... args) {
     if (M < 1 || M > 64) return false;
-    if (M == 1) *out = F::template get<1, true>(args...);
-    else if (M == 2) *out = F::template get<2, true>(args...);
-    else if (M == 3) *out = F::template get<4, false>(args...);
-    else if (M == 4) *out = F::template get<4, true>(args...);
-    else if (M < 8) *out = F::template get<8, false>(args...);
-    else if (M == 8) *out = F::template get<8, true>(args...);
-    else if (M < 16) *out = F::template get<16, false>(args...);
-    else if (M == 16) *out = F::template get<16, true>(args...);
-    else if (M < 32) *out = F::template get<32, false>(args...);
-    else if (M == 32) *out = F::template get<32, true>(args...);
-    else if (M < 64) *out = F::template get<64, false>(args...);
-    else *out = F::template get<64, true>(args...);
-    return true;
+    switch (worker_class(M)) {
+        case 4: *out = F::template get<4, false>(args...); return true;
+        case 6: *out = F::template get<6, false>(args...); return true;
+        case 8: *out = F::template get<8, false>(args...); return true;
+        case 10: *out = F::template get<10, false>(args...); return true;
+        case 12: *out = F::template get<12, false>(args...); return true;
+        case 14: *out = F::template get<14, false>(args...); return true;
+        case 16: *out = F::template get<16, false>(args...); return true;
+        case 20: *out = F::template get<20, false>(args...); return true;
+        case 24: *out = F::template get<24, false>(args...); return true;
+        case 28: *out = F::template get<28, false>(args...); return true;
+        case 32: *out = F::template get<32, false>(args...); return true;
+        case 40: *out = F::template get<40, false>(args...); return true;
+        case 48: *out = F::template get<48, false>(args...); return true;
+        case 56: *out = F::template get<56, false>(args...); return true;
+        case 64: *out = F::template get<64, false>(args...); return true;
+        default: return false;
+    }
 }
 
 // Defined per storage type.  k1, k2: Mix kinds (kIdentity, kGlobal, kTable);
@@ -1272,13 +1329,19 @@ bool select_workers(int M, Out *out, A... args) {
 // one exists, else the one that reads the kinds at run time.  Returns false
 // if M is outside [1, 64].
 bool kernels_f32(int M, int k1, int k2, bool subset, KernelSet *out);
+bool kernels_f32_class(int M, int k1, int k2, bool subset, KernelSet *out);
 bool kernels_bf16(int M, int k1, int k2, bool subset, KernelSet *out);
+bool kernels_bf16_class(int M, int k1, int k2, bool subset, KernelSet *out);
 // Step kernels that also mix the optimizer state with Mix1.
 bool kernels_f32_ms(int M, int k1, int k2, bool subset, KernelSet *out);
+bool kernels_f32_ms_class(int M, int k1, int k2, bool subset, KernelSet *out);
 bool kernels_bf16_ms(int M, int k1, int k2, bool subset, KernelSet *out);
+bool kernels_bf16_ms_class(int M, int k1, int k2, bool subset, KernelSet *out);
 // Split-execution kernels.
 bool split_kernels_f32(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out);
+bool split_kernels_f32_class(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out);
 bool split_kernels_bf16(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out);
+bool split_kernels_bf16_class(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out);
 // The access-pattern reference for exact M in {1, 2, 4, 8, 16, 32, 64}: the
 // pattern_kernel instance, its lane vector and the step's blocks per CU.
 bool pattern_kernel_for(int M, bool bf16, const void **kernel, int *v, int *blocks_per_cu);

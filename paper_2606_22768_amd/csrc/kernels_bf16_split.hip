@@ -14,7 +14,7 @@ struct Sets {
 }  // namespace
 
 bool split_kernels_bf16(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out) {
-    return select_workers<Sets>(M, out, k1, k2, subset, mix_state);
+    return exact_workers(M) ? select_exact<Sets>(M, out, k1, k2, subset, mix_state) : split_kernels_bf16_class(M, k1, k2, subset, mix_state, out);
 }
 
 }  // namespace fgd

@@ -281,18 +281,19 @@ TopoStatus build_mix_topology(int32_t M, int32_t kind, const int32_t *row_ptr, c
     return TopoStatus::ok;
 }
 
-void MixTopology::pack_tables(std::vector<int32_t> &out) const {
+void MixTopology::pack_tables(std::vector<int32_t> &out, int32_t stride) const {
     out.clear();
     if (kind != 2) return;
     const int32_t M = num_workers;
     const int32_t nnz = row_ptr[M];
-    out.assign(static_cast<size_t>(rounds) * width * M * 2, 0);
+    const int32_t S = stride > M ? stride : M;
+    out.assign(static_cast<size_t>(rounds) * width * S * 2, 0);
     for (int32_t k = 0; k < rounds; ++k) {
         for (int32_t m = 0; m < M; ++m) {
             int32_t d = 0;
             for (int32_t e = row_ptr[m]; e < row_ptr[m + 1]; ++e) {
                 if (!live[static_cast<size_t>(k) * nnz + e]) continue;
-                const size_t at = ((static_cast<size_t>(k) * width + d) * M + m) * 2;
+                const size_t at = ((static_cast<size_t>(k) * width + d) * S + m) * 2;
                 float w = eff[static_cast<size_t>(k) * nnz + e];
                 int32_t bits;
                 static_assert(sizeof bits == sizeof w, "float is 32-bit");
@@ -303,7 +304,7 @@ void MixTopology::pack_tables(std::vector<int32_t> &out) const {
                 ++d;
             }
             for (; d < width; ++d) {
-                const size_t at = ((static_cast<size_t>(k) * width + d) * M + m) * 2;
+                const size_t at = ((static_cast<size_t>(k) * width + d) * S + m) * 2;
                 out[at] = M;  // the all-zero LDS row
                 out[at + 1] = 0;
             }

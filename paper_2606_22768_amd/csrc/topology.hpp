@@ -31,10 +31,11 @@ struct MixTopology {
     // Rounds of this slot as the kernel counts them (global mean = 1).
     int32_t effective_rounds() const { return kind == 0 ? 0 : (kind == 1 ? 1 : rounds); }
 
-    // Padded per-round tables for the kernel: [rounds][width][M] pairs of
-    // (column, float bits); the d-th live entry of each row in ascending
-    // column order, then (M, 0) padding that points at an all-zero row.
-    void pack_tables(std::vector<int32_t> &out) const;
+    // Padded per-round tables for the kernel: [rounds][width][stride] pairs
+    // of (column, float bits), stride >= M (0: M); the d-th live entry of
+    // each row in ascending column order, then (M, 0) padding that points at
+    // an all-zero row; (0, 0) for the rows from M to stride.
+    void pack_tables(std::vector<int32_t> &out, int32_t stride = 0) const;
 };
 
 // Validates the inputs and fills `out`.  On failure `err` says why.
