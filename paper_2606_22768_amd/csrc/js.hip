@@ -15,7 +15,8 @@
 // Probabilities are those of the full softmax; only the sum is restricted to
 // T.  Kernels, in order on the call's stream, with a caller workspace between
 // them:
-//   js_rows_kernel         streams all (M + 1) U rows once (persistent, no
+//   js_rows_kernel         (few rows: js_rows_split_kernel, a row per block)
+//                          streams all (M + 1) U rows once (persistent, no
 //                          barriers): per row, each wave's (shift, sum) part
 //                          of the log-sum-exp; per averaged row, each row
 //                          thread's four largest vector maxima (key, index)
@@ -637,10 +638,12 @@ __device__ __forceinline__ void vec_terms(u32x4 cur, int64_t i0, int64_t K, uint
 // whole for every lane: their loads take the sweep's offset as a scalar.
 // With kAvg it also keeps the thread's kTopVecs largest vector maxima (top,
 // empty on entry; indices past 16 bits wrap, and the per-token wave kernel
-// is then not used).
+// is then not used).  A split row's segment passes its own first element and
+// sweep count (at least 1), and s_first, its first sweep of the row.
 template <class E, bool kAvg>
 __device__ inline void row_terms(rsrc_t r, rsrc_t rn, bool has_next, int64_t i_first, int64_t K, int nsw,
-                                 u32x4 &nxt, RowLse &st, const double *etab, const double *tab, TopVecs<E> &top) {
+                                 u32x4 &nxt, RowLse &st, const double *etab, const double *tab, TopVecs<E> &top,
+                                 int s_first = 0) {
     constexpr int64_t kStride = static_cast<int64_t>(kRowThreads) * E::kPer;
     constexpr uint32_t kSweepBytes = kRowThreads * 16;
     const uint32_t voff = static_cast<uint32_t>(i_first * E::kElem);
@@ -649,16 +652,17 @@ __device__ inline void row_terms(rsrc_t r, rsrc_t rn, bool has_next, int64_t i_f
     for (; s < nsw - 2; ++s) {
         const u32x4 cur = nxt;
         nxt = __builtin_amdgcn_raw_buffer_load_b128(r, voff, (s + 1) * kSweepBytes, kLoadPolicy);
-        vec_terms<E, kAvg, true>(cur, 0, K, static_cast<uint32_t>(s), st, etab, tab, top);
+        vec_terms<E, kAvg, true>(cur, 0, K, static_cast<uint32_t>(s_first + s), st, etab, tab, top);
     }
     if (nsw >= 2) {  // s = nsw - 2: the next load is the last sweep's, which a lane may lack
         const u32x4 cur = nxt;
         if (i_last < K) nxt = __builtin_amdgcn_raw_buffer_load_b128(r, voff, (nsw - 1) * kSweepBytes, kLoadPolicy);
-        vec_terms<E, kAvg, true>(cur, 0, K, static_cast<uint32_t>(nsw - 2), st, etab, tab, top);
+        vec_terms<E, kAvg, true>(cur, 0, K, static_cast<uint32_t>(s_first + nsw - 2), st, etab, tab, top);
     }
     const u32x4 cur = nxt;
     if (has_next && i_first < K) nxt = __builtin_amdgcn_raw_buffer_load_b128(rn, voff, 0, kLoadPolicy);
-    if (i_last < K) vec_terms<E, kAvg, false>(cur, i_last, K, static_cast<uint32_t>(nsw - 1), st, etab, tab, top);
+    if (i_last < K)
+        vec_terms<E, kAvg, false>(cur, i_last, K, static_cast<uint32_t>(s_first + nsw - 1), st, etab, tab, top);
 }
 
 // Every row's wave parts of its log-sum-exp, and the averaged rows'
@@ -711,6 +715,72 @@ void js_rows_kernel(JsParams a, JsWork w) {
         const LsePart p = wave_lse(ml, sl, tab);
         if ((threadIdx.x & (kWave - 1)) == 0) w.part[r * kRowWaves + lt / kWave] = p;
         if (avg) w.top[r * kRowThreads + lt] = u32x4{top.t[0], top.t[1], top.t[2], top.t[3]};
+    }
+}
+
+// js_rows_kernel for calls of few rows, where a row's chain of load latencies
+// and float64 exps bounds the call: block q takes the row at position q of
+// the streaming order, its kSplit thread groups an equal run of the row's
+// sweeps each (the last group the rest, at least one: kSplitMinSweeps).  The
+// groups' wave parts and vector maxima are merged in LDS, so the workspace is
+// js_rows_kernel's, with the same maxima, and an averaged row and a worker
+// row still run the same sums.  The row's first load is in flight while the
+// tables are filled.  js_launch_rows has the times and the choice.
+constexpr int64_t kSplitMinSweeps = 16;  // below it the merge costs what a shorter chain gains (5 sweeps, 600 rows:
+                                         // 37.3 us a call with one group a row, 37.7 with two, 41.8 with four)
+template <class E, int kSplit>
+__global__ __launch_bounds__(kRowThreads * kSplit) __attribute__((amdgpu_waves_per_eu(kSplit == 2 ? 6 : 4, 8)))
+void js_rows_split_kernel(JsParams a, JsWork w) {
+    constexpr int64_t kStride = static_cast<int64_t>(kRowThreads) * E::kPer;
+    __shared__ double etab[E::kBf16 ? kBfTabEntries : 1];
+    __shared__ double tab[kTab];
+    __shared__ LsePart s_part[kSplit][kRowWaves];
+    __shared__ u32x4 s_top[kSplit - 1][kRowThreads];
+    const int lt = threadIdx.x % kRowThreads;
+    const int seg = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kRowThreads));
+    const int nsw = static_cast<int>((a.K + kStride - 1) / kStride);  // sweeps per row
+    const int per = (nsw + kSplit - 1) / kSplit;
+    const int s0 = seg * per;                                         // this group's first sweep
+    const int ns = nsw - s0 < per ? nsw - s0 : per;
+    const int64_t i_first = static_cast<int64_t>(lt) * E::kPer + static_cast<int64_t>(s0) * kStride;
+    const int64_t r = js_stream_row(blockIdx.x, a.M, a.U);
+    const bool avg = r < a.U;
+    const rsrc_t rr = avg ? js_row(a.avg, r, a.ldk, E::kElem) : js_row(a.workers, r - a.U, a.ldk, E::kElem);
+    u32x4 nxt = {0, 0, 0, 0};
+    if (i_first < a.K)
+        nxt = __builtin_amdgcn_raw_buffer_load_b128(rr, static_cast<uint32_t>(i_first * E::kElem), 0, kLoadPolicy);
+    if constexpr (E::kBf16) fill_bf16_exp_table(etab);
+    load_exp_table(tab);  // its barrier also covers etab
+    RowLse st;
+    TopVecs<E> top;
+    if (avg)
+        row_terms<E, true>(rr, rr, false, i_first, a.K, ns, nxt, st, etab, tab, top, s0);
+    else
+        row_terms<E, false>(rr, rr, false, i_first, a.K, ns, nxt, st, etab, tab, top, s0);
+    double ml, sl;
+    row_lse_lane(st, ml, sl, tab);
+    const LsePart p = wave_lse(ml, sl, tab);
+    if ((threadIdx.x & (kWave - 1)) == 0) s_part[seg][lt / kWave] = p;
+    if (avg && seg > 0) s_top[seg - 1][lt] = u32x4{top.t[0], top.t[1], top.t[2], top.t[3]};
+    __syncthreads();
+    if (seg > 0) return;
+    if (lt < kRowWaves) {  // the groups' parts, in order, about the largest shift
+        double m = s_part[0][lt].m, s = 0.0;
+#pragma unroll
+        for (int j = 1; j < kSplit; ++j) m = fmax(m, s_part[j][lt].m);
+#pragma unroll
+        for (int j = 0; j < kSplit; ++j)
+            if (s_part[j][lt].s != 0.0) s += s_part[j][lt].s * exp_table(s_part[j][lt].m - m, tab);
+        w.part[r * kRowWaves + lt] = LsePart{m, s};
+    }
+    if (avg) {
+#pragma unroll
+        for (int j = 0; j < kSplit - 1; ++j) {
+            const u32x4 t = s_top[j][lt];
+#pragma unroll
+            for (int i = 0; i < kTopVecs; ++i) top.insert(t[i]);
+        }
+        w.top[r * kRowThreads + lt] = u32x4{top.t[0], top.t[1], top.t[2], top.t[3]};
     }
 }
 
@@ -1107,6 +1177,47 @@ __device__ inline void select_sorted(const uint64_t *comp, int C, int k, int lan
     }
 }
 
+// A token's JS terms (js_token_wave_kernel), 64 / kLanes workers at a time:
+// worker jw of the group takes lanes [jw, jw + 1) * kLanes, lane l of them the
+// selected tokens l, l + kLanes, ... in index order; their sum is d's.  The
+// workers' log-sum-exp parts are loaded while the first gathers are in flight.
+template <class E, int kLanes, class Lds>
+__device__ __forceinline__ void wave_js_terms(const JsParams &a, const JsWork &w, Lds &L, int64_t u, int lane,
+                                              const double *tab) {
+    const int k = a.k;
+    constexpr int kGroup = kWave / kLanes;
+    constexpr double kLog2 = 0.69314718055994530942;
+    const int jw = lane / kLanes, l = lane % kLanes;
+    for (int64_t w0 = 0; w0 < a.M; w0 += kGroup) {
+        const int nw = a.M - w0 < kGroup ? static_cast<int>(a.M - w0) : kGroup;
+        const bool mine_w = jw < nw;
+        const int64_t row = (w0 + (mine_w ? jw : 0)) * a.U + u;
+        const char *zrow = static_cast<const char *>(a.workers) + row * a.ldk * E::kElem;
+        double acc = 0.0;
+        for (int t0 = 0; t0 < k; t0 += kWaveGather * kLanes) {
+            float z[kWaveGather];
+#pragma unroll
+            for (int q = 0; q < kWaveGather; ++q) {
+                const int t = t0 + l + q * kLanes;
+                z[q] = mine_w && t < k ? E::at_ptr(zrow, L.u.out.idx[t]) : 0.0f;
+            }
+            if (t0 == 0) {
+                if (lane < nw) L.lse[lane] = row_lse(w.part + (a.U + (w0 + lane) * a.U + u) * kRowWaves, tab);
+                wave_sync();
+            }
+            const double lse_w = L.lse[mine_w ? jw : 0];
+#pragma unroll
+            for (int q = 0; q < kWaveGather; ++q) {
+                const int t = t0 + l + q * kLanes;
+                if (mine_w && t < k) acc += js_term(static_cast<double>(z[q]) - lse_w, L.u.out.la[t]);
+            }
+        }
+        for (int o = kLanes / 2; o > 0; o >>= 1) acc += shfl_xor_d(acc, o);
+        if (l == 0 && mine_w) a.d_out[row] = sqrt((acc > 0.0 ? acc : 0.0) / kLog2);
+        wave_sync();  // L.lse is rewritten by the next group
+    }
+}
+
 // Per token, one wave (token u = blockIdx.x * kWaveTokens + wave; no block
 // barriers after the exp table): the averaged row's log-sum-exp from its
 // wave parts; T0, the k-th largest of the 1024 recorded vector maxima (16-bit
@@ -1117,7 +1228,7 @@ __device__ inline void select_sorted(const uint64_t *comp, int C, int k, int lan
 // their elements at or above T0 are appended to the candidates in lane
 // order; the candidates are sorted under (key descending, index ascending)
 // by a bitonic network across the wave, the first k then by index; then
-// the JS terms, kJsLanes lanes per worker, with a lane's gathers issued
+// the JS terms, at least kJsLanes lanes per worker, with a lane's gathers issued
 // together.  A token with more than kCand candidates (a row of many equal
 // logits) is flagged and left to js_token_radix_kernel.  k <= kCand / 2:
 // kCand 512 keeps a block's LDS at 35 KB, 1024 (for 256 < k <= 512) takes
@@ -1263,40 +1374,19 @@ void js_token_wave_kernel(JsParams a, JsWork w) {
     if (a.topk_out)
         for (int t = lane; t < k; t += kWave) a.topk_out[u * k + t] = L.u.out.idx[t];
 
-    // JS terms, kJsGroup workers at a time: worker jw of the group takes
-    // lanes [jw, jw + 1) * kJsLanes, lane l of them the selected tokens l,
-    // l + kJsLanes, ... in index order; their sum is d's.  The workers'
-    // log-sum-exp parts are loaded while the first gathers are in flight.
-    constexpr double kLog2 = 0.69314718055994530942;
-    const int jw = lane / kJsLanes, l = lane % kJsLanes;
-    for (int64_t w0 = 0; w0 < a.M; w0 += kJsGroup) {
-        const int nw = a.M - w0 < kJsGroup ? static_cast<int>(a.M - w0) : kJsGroup;
-        const bool mine_w = jw < nw;
-        const int64_t row = (w0 + (mine_w ? jw : 0)) * a.U + u;
-        const char *zrow = static_cast<const char *>(a.workers) + row * a.ldk * E::kElem;
-        double acc = 0.0;
-        for (int t0 = 0; t0 < k; t0 += kWaveGather * kJsLanes) {
-            float z[kWaveGather];
-#pragma unroll
-            for (int q = 0; q < kWaveGather; ++q) {
-                const int t = t0 + l + q * kJsLanes;
-                z[q] = mine_w && t < k ? E::at_ptr(zrow, L.u.out.idx[t]) : 0.0f;
-            }
-            if (t0 == 0) {
-                if (lane < nw) L.lse[lane] = row_lse(w.part + (a.U + (w0 + lane) * a.U + u) * kRowWaves, tab);
-                wave_sync();
-            }
-            const double lse_w = L.lse[mine_w ? jw : 0];
-#pragma unroll
-            for (int q = 0; q < kWaveGather; ++q) {
-                const int t = t0 + l + q * kJsLanes;
-                if (mine_w && t < k) acc += js_term(static_cast<double>(z[q]) - lse_w, L.u.out.la[t]);
-            }
-        }
-        for (int o = kJsLanes / 2; o > 0; o >>= 1) acc += shfl_xor_d(acc, o);
-        if (l == 0 && mine_w) a.d_out[row] = sqrt((acc > 0.0 ? acc : 0.0) / kLog2);
-        wave_sync();  // L.lse is rewritten by the next group
-    }
+    // Up to four workers share all of the wave's lanes: a lane's chain of
+    // terms (an exp, a log1p and a gather each) bounds a call of few tokens.
+    // Us per call, 8 lanes a worker -> this: 2 workers x 85 tokens k = 100
+    // 48 -> 37 and k = 400 144 -> 98; 1 x 30 52 -> 33 and 147 -> 80.  The
+    // number of lanes is a constant: at run time it cost 8 workers 2.5 us.
+    if (a.M > 4)
+        wave_js_terms<E, kJsLanes>(a, w, L, u, lane, tab);
+    else if (a.M > 2)
+        wave_js_terms<E, kWave / 4>(a, w, L, u, lane, tab);
+    else if (a.M == 2)
+        wave_js_terms<E, kWave / 2>(a, w, L, u, lane, tab);
+    else
+        wave_js_terms<E, kWave>(a, w, L, u, lane, tab);
     if (lane == 0) w.flag[u] = 0;
 }
 
@@ -1316,6 +1406,30 @@ __global__ __launch_bounds__(256) void js_mean_kernel(const double *d, int64_t U
 }
 
 namespace {
+template <class E>
+void js_launch_rows(const JsParams &p, const JsWork &w, int num_cus, hipStream_t stream) {
+    const int64_t cus = std::max(num_cus, 1), R = (static_cast<int64_t>(p.M) + 1) * p.U;
+    // A row per block of four groups while every CU has at most one row, of
+    // two groups while all rows fit the chip's blocks at once (us per call of
+    // 8 workers over 128256 tokens, one / two / four groups a row: 252 rows
+    // float32 101 / 75 / 68, bf16 76 / 62 / 55; 360 rows float32 104 / 84 / 89,
+    // bf16 78 / 66 / 67; 765 rows float32 124 / 118 / 116, bf16 87 / 75 / 80).
+    // With more rows the groups' merge costs what the finer last pass gains
+    // (1530 rows over 50256 tokens: float32 99 / 100 / 107, bf16 69 / 70 / 81).
+    const int64_t sweeps = js_thread_vectors(p.K, E::kPer);
+    if (sweeps >= kSplitMinSweeps && R <= cus) {
+        hipLaunchKernelGGL((js_rows_split_kernel<E, 4>), dim3(static_cast<unsigned>(R)), dim3(kRowThreads * 4), 0,
+                           stream, p, w);
+    } else if (sweeps >= kSplitMinSweeps && R <= kRowsBlocksPerCu * cus) {
+        hipLaunchKernelGGL((js_rows_split_kernel<E, 2>), dim3(static_cast<unsigned>(R)), dim3(kRowThreads * 2), 0,
+                           stream, p, w);
+    } else {
+        const int64_t groups = (R + kRowsPerBlock - 1) / kRowsPerBlock;
+        hipLaunchKernelGGL(js_rows_kernel<E>, dim3(static_cast<unsigned>(std::min(groups, kRowsBlocksPerCu * cus))),
+                           dim3(kRowsBlock), 0, stream, p, w);
+    }
+}
+
 int64_t js_part_bytes(int32_t M, int64_t U) {
     return (static_cast<int64_t>(M) + 1) * U * kRowWaves * static_cast<int64_t>(sizeof(LsePart));
 }
@@ -1335,8 +1449,6 @@ bool js_launch(const void *avg, const void *workers, int32_t bf16, int32_t M, in
     const int64_t o_top = js_part_bytes(M, U), o_flag = o_top + js_top_bytes(U);
     JsWork w{reinterpret_cast<LsePart *>(ws), reinterpret_cast<u32x4 *>(ws + o_top),
              reinterpret_cast<int32_t *>(ws + o_flag)};
-    const int64_t groups = ((static_cast<int64_t>(M) + 1) * U + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int64_t grid = std::min<int64_t>(groups, static_cast<int64_t>(kRowsBlocksPerCu) * std::max(num_cus, 1));
     const dim3 token_waves(static_cast<unsigned>((U + kWaveTokens - 1) / kWaveTokens));
     // The wave kernel names a row thread's vectors by 16-bit indices.
     const bool wave_path =
@@ -1345,7 +1457,7 @@ bool js_launch(const void *avg, const void *workers, int32_t bf16, int32_t M, in
     // flagged ones (few): then a few blocks per CU walk the flags.
     const dim3 tokens(static_cast<unsigned>(wave_path ? std::min<int64_t>(U, 4 * std::max(num_cus, 1)) : U));
     if (bf16) {
-        hipLaunchKernelGGL(js_rows_kernel<JsBF16>, dim3(static_cast<unsigned>(grid)), dim3(kRowsBlock), 0, stream, p, w);
+        js_launch_rows<JsBF16>(p, w, num_cus, stream);
         if (wave_path && k <= kWaveCandSmall / 2)
             hipLaunchKernelGGL((js_token_wave_kernel<JsBF16, kWaveCandSmall>), token_waves, dim3(kBlock), 0, stream, p, w);
         else if (wave_path)
@@ -1353,7 +1465,7 @@ bool js_launch(const void *avg, const void *workers, int32_t bf16, int32_t M, in
         hipLaunchKernelGGL(js_token_radix_kernel<JsBF16>, tokens, dim3(kBlock), 0, stream, p, w,
                            wave_path ? static_cast<const int32_t *>(w.flag) : nullptr);
     } else {
-        hipLaunchKernelGGL(js_rows_kernel<JsF32>, dim3(static_cast<unsigned>(grid)), dim3(kRowsBlock), 0, stream, p, w);
+        js_launch_rows<JsF32>(p, w, num_cus, stream);
         if (wave_path && k <= kWaveCandSmall / 2)
             hipLaunchKernelGGL((js_token_wave_kernel<JsF32, kWaveCandSmall>), token_waves, dim3(kBlock), 0, stream, p, w);
         else if (wave_path)
