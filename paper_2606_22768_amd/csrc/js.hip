@@ -1181,14 +1181,17 @@ __device__ inline void select_sorted(const uint64_t *comp, int C, int k, int lan
 // worker jw of the group takes lanes [jw, jw + 1) * kLanes, lane l of them the
 // selected tokens l, l + kLanes, ... in index order; their sum is d's.  The
 // workers' log-sum-exp parts are loaded while the first gathers are in flight.
-template <class E, int kLanes, class Lds>
-__device__ __forceinline__ void wave_js_terms(const JsParams &a, const JsWork &w, Lds &L, int64_t u, int lane,
-                                              const double *tab) {
+// With kShare the block's waves take the groups in turn.
+template <class E, int kLanes, bool kShare, class Lds>
+__device__ __forceinline__ void wave_js_terms(const JsParams &a, const JsWork &w, Lds &L, int64_t u, int wave,
+                                              int lane, const double *tab) {
     const int k = a.k;
     constexpr int kGroup = kWave / kLanes;
+    static_assert(kGroup * (kShare ? kBlock / kWave : 1) <= kJsGroup, "L.lse holds the workers at work");
+    double *lse = L.lse + (kShare ? wave * kGroup : 0);
     constexpr double kLog2 = 0.69314718055994530942;
     const int jw = lane / kLanes, l = lane % kLanes;
-    for (int64_t w0 = 0; w0 < a.M; w0 += kGroup) {
+    for (int64_t w0 = kShare ? wave * kGroup : 0; w0 < a.M; w0 += kGroup * (kShare ? kBlock / kWave : 1)) {
         const int nw = a.M - w0 < kGroup ? static_cast<int>(a.M - w0) : kGroup;
         const bool mine_w = jw < nw;
         const int64_t row = (w0 + (mine_w ? jw : 0)) * a.U + u;
@@ -1202,10 +1205,10 @@ __device__ __forceinline__ void wave_js_terms(const JsParams &a, const JsWork &w
                 z[q] = mine_w && t < k ? E::at_ptr(zrow, L.u.out.idx[t]) : 0.0f;
             }
             if (t0 == 0) {
-                if (lane < nw) L.lse[lane] = row_lse(w.part + (a.U + (w0 + lane) * a.U + u) * kRowWaves, tab);
+                if (lane < nw) lse[lane] = row_lse(w.part + (a.U + (w0 + lane) * a.U + u) * kRowWaves, tab);
                 wave_sync();
             }
-            const double lse_w = L.lse[mine_w ? jw : 0];
+            const double lse_w = lse[mine_w ? jw : 0];
 #pragma unroll
             for (int q = 0; q < kWaveGather; ++q) {
                 const int t = t0 + l + q * kLanes;
@@ -1214,51 +1217,19 @@ __device__ __forceinline__ void wave_js_terms(const JsParams &a, const JsWork &w
         }
         for (int o = kLanes / 2; o > 0; o >>= 1) acc += shfl_xor_d(acc, o);
         if (l == 0 && mine_w) a.d_out[row] = sqrt((acc > 0.0 ? acc : 0.0) / kLog2);
-        wave_sync();  // L.lse is rewritten by the next group
+        wave_sync();  // lse is rewritten by the next group
     }
 }
 
-// Per token, one wave (token u = blockIdx.x * kWaveTokens + wave; no block
-// barriers after the exp table): the averaged row's log-sum-exp from its
-// wave parts; T0, the k-th largest of the 1024 recorded vector maxima (16-bit
-// keys, built from the top bit down by counting with ballots), which is at
-// most the row's k-th largest key, so the selected tokens are among the
-// elements with key >= T0 (on these inputs a little over k); the vectors
-// whose maxima reach T0 go to a queue and are read again in one round, and
-// their elements at or above T0 are appended to the candidates in lane
-// order; the candidates are sorted under (key descending, index ascending)
-// by a bitonic network across the wave, the first k then by index; then
-// the JS terms, at least kJsLanes lanes per worker, with a lane's gathers issued
-// together.  A token with more than kCand candidates (a row of many equal
-// logits) is flagged and left to js_token_radix_kernel.  k <= kCand / 2:
-// kCand 512 keeps a block's LDS at 35 KB, 1024 (for 256 < k <= 512) takes
-// 58 KB.
+// One token's selection, by one wave: into L.u.out the selected tokens in
+// index order with log pbar, and into topk_out.  False (in every lane, with
+// the token's flag set) when it is left to js_token_radix_kernel.
 template <class E, int kCand>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kCand == kWaveCandSmall ? 4 : 2, 8)))
-void js_token_wave_kernel(JsParams a, JsWork w) {
+__device__ __forceinline__ bool wave_select(const JsParams &a, const JsWork &w, WaveLds<kCand> &L, int64_t u, int lane,
+                                            const u32x4 (&tq)[kRtPerLane], const LsePart (&pa)[kRowWaves],
+                                            const double *tab) {
     constexpr int P = E::kPer;
     constexpr int64_t kStride = static_cast<int64_t>(kRowThreads) * P;  // elements per row sweep
-    __shared__ double tab[kTab];
-    __shared__ WaveLds<kCand> lds[kWaveTokens];
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t u = static_cast<int64_t>(blockIdx.x) * kWaveTokens + wave;
-    const bool live = u < a.U;  // the whole wave
-
-    // The largest vector maxima of row threads lane + q kWave (entries
-    // key16 << 16 | vector index, largest first; 0: none) and the averaged
-    // row's wave parts, loaded while the exp table is.
-    u32x4 tq[kRtPerLane];
-    LsePart pa[kRowWaves];
-    if (live) {
-#pragma unroll
-        for (int q = 0; q < kRtPerLane; ++q) tq[q] = w.top[u * kRowThreads + lane + q * kWave];
-#pragma unroll
-        for (int j = 0; j < kRowWaves; ++j) pa[j] = w.part[u * kRowWaves + j];
-    }
-    load_exp_table(tab);
-    if (!live) return;
-    WaveLds<kCand> &L = lds[wave];
     const int k = a.k;
     const rsrc_t ra = js_row(a.avg, u, a.ldk, E::kElem);
     const double lse_a = lse_of_parts(pa, tab);
@@ -1357,7 +1328,7 @@ void js_token_wave_kernel(JsParams a, JsWork w) {
     const int C = __builtin_amdgcn_readfirstlane(nsel);
     if (C > kCand || C < k) {  // the same in every lane
         if (lane == 0) w.flag[u] = 1;
-        return;
+        return false;
     }
     wave_sync();
 
@@ -1374,19 +1345,80 @@ void js_token_wave_kernel(JsParams a, JsWork w) {
     if (a.topk_out)
         for (int t = lane; t < k; t += kWave) a.topk_out[u * k + t] = L.u.out.idx[t];
 
+    return true;
+}
+
+// Per token, one wave (token u = blockIdx.x * kWaveTokens + wave; no block
+// barriers after the exp table): the averaged row's log-sum-exp from its
+// wave parts; T0, the k-th largest of the 1024 recorded vector maxima (16-bit
+// keys, built from the top bit down by counting with ballots), which is at
+// most the row's k-th largest key, so the selected tokens are among the
+// elements with key >= T0 (on these inputs a little over k); the vectors
+// whose maxima reach T0 go to a queue and are read again in one round, and
+// their elements at or above T0 are appended to the candidates in lane
+// order; the candidates are sorted under (key descending, index ascending)
+// by a bitonic network across the wave, the first k then by index; then
+// the JS terms, at least kJsLanes lanes per worker, with a lane's gathers issued
+// together.  A token with more than kCand candidates (a row of many equal
+// logits) is flagged and left to js_token_radix_kernel.  k <= kCand / 2:
+// kCand 512 keeps a block's LDS at 35 KB, 1024 (for 256 < k <= 512) takes
+// 58 KB.
+// With kShare (few tokens) a block takes one token: its first wave selects,
+// then all four share the JS terms, whose chain of exps, logarithms and
+// gathers in each lane bounds such a call.
+template <class E, int kCand, bool kShare>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kCand == kWaveCandSmall ? 4 : 2, 8)))
+void js_token_wave_kernel(JsParams a, JsWork w) {
+    __shared__ double tab[kTab];
+    __shared__ WaveLds<kCand> lds[kShare ? 1 : kWaveTokens];
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t u = kShare ? blockIdx.x : static_cast<int64_t>(blockIdx.x) * kWaveTokens + wave;
+    const bool selects = kShare ? wave == 0 : u < a.U;  // the whole wave
+
+    // The largest vector maxima of row threads lane + q kWave (entries
+    // key16 << 16 | vector index, largest first; 0: none) and the averaged
+    // row's wave parts, loaded while the exp table is.
+    u32x4 tq[kRtPerLane];
+    LsePart pa[kRowWaves];
+    if (selects) {
+#pragma unroll
+        for (int q = 0; q < kRtPerLane; ++q) tq[q] = w.top[u * kRowThreads + lane + q * kWave];
+#pragma unroll
+        for (int j = 0; j < kRowWaves; ++j) pa[j] = w.part[u * kRowWaves + j];
+    }
+    load_exp_table(tab);
+    WaveLds<kCand> &L = lds[kShare ? 0 : wave];
+    if constexpr (kShare) {
+        __shared__ int s_selected;
+        if (selects) {
+            const bool ok = wave_select<E, kCand>(a, w, L, u, lane, tq, pa, tab);
+            if (lane == 0) s_selected = ok;
+        }
+        __syncthreads();
+        if (!s_selected) return;
+        if (a.M > kWaveTokens)
+            wave_js_terms<E, kWave / 2, true>(a, w, L, u, wave, lane, tab);
+        else
+            wave_js_terms<E, kWave, true>(a, w, L, u, wave, lane, tab);
+        if (threadIdx.x == 0) w.flag[u] = 0;
+        return;
+    }
+    if (!selects || !wave_select<E, kCand>(a, w, L, u, lane, tq, pa, tab)) return;
+
     // Up to four workers share all of the wave's lanes: a lane's chain of
     // terms (an exp, a log1p and a gather each) bounds a call of few tokens.
     // Us per call, 8 lanes a worker -> this: 2 workers x 85 tokens k = 100
     // 48 -> 37 and k = 400 144 -> 98; 1 x 30 52 -> 33 and 147 -> 80.  The
     // number of lanes is a constant: at run time it cost 8 workers 2.5 us.
     if (a.M > 4)
-        wave_js_terms<E, kJsLanes>(a, w, L, u, lane, tab);
+        wave_js_terms<E, kJsLanes, false>(a, w, L, u, wave, lane, tab);
     else if (a.M > 2)
-        wave_js_terms<E, kWave / 4>(a, w, L, u, lane, tab);
+        wave_js_terms<E, kWave / 4, false>(a, w, L, u, wave, lane, tab);
     else if (a.M == 2)
-        wave_js_terms<E, kWave / 2>(a, w, L, u, lane, tab);
+        wave_js_terms<E, kWave / 2, false>(a, w, L, u, wave, lane, tab);
     else
-        wave_js_terms<E, kWave>(a, w, L, u, lane, tab);
+        wave_js_terms<E, kWave, false>(a, w, L, u, wave, lane, tab);
     if (lane == 0) w.flag[u] = 0;
 }
 
@@ -1430,6 +1462,36 @@ void js_launch_rows(const JsParams &p, const JsWork &w, int num_cus, hipStream_t
     }
 }
 
+template <class E, int kCand>
+void js_launch_wave(const JsParams &p, const JsWork &w, int num_cus, hipStream_t stream) {
+    // A block per token up to two tokens per CU, three where k > 256 (us per
+    // call over 9000 float32 tokens, a wave / a block per token: 8 workers,
+    // 256 tokens k = 100 55 / 46, k = 300 106 / 78, 600 tokens k = 100
+    // 82 / 80, k = 300 134 / 118, 1024 tokens 116 / 118 and 170 / 166, 1500
+    // tokens 162 / 174 and 221 / 257; 1 worker, 256 tokens 31 / 30 and
+    // 60 / 58): with more, the waves that wait for the selection take the
+    // places of others' selections.
+    if (p.U <= static_cast<int64_t>(kCand == kWaveCandSmall ? 2 : 3) * std::max(num_cus, 1))
+        hipLaunchKernelGGL((js_token_wave_kernel<E, kCand, true>), dim3(static_cast<unsigned>(p.U)), dim3(kBlock), 0,
+                           stream, p, w);
+    else
+        hipLaunchKernelGGL((js_token_wave_kernel<E, kCand, false>),
+                           dim3(static_cast<unsigned>((p.U + kWaveTokens - 1) / kWaveTokens)), dim3(kBlock), 0, stream,
+                           p, w);
+}
+
+template <class E>
+void js_launch_tokens(const JsParams &p, const JsWork &w, bool wave_path, dim3 radix_grid, int num_cus,
+                      hipStream_t stream) {
+    js_launch_rows<E>(p, w, num_cus, stream);
+    if (wave_path && p.k <= kWaveCandSmall / 2)
+        js_launch_wave<E, kWaveCandSmall>(p, w, num_cus, stream);
+    else if (wave_path)
+        js_launch_wave<E, kWaveCandLarge>(p, w, num_cus, stream);
+    hipLaunchKernelGGL(js_token_radix_kernel<E>, radix_grid, dim3(kBlock), 0, stream, p, w,
+                       wave_path ? static_cast<const int32_t *>(w.flag) : nullptr);
+}
+
 int64_t js_part_bytes(int32_t M, int64_t U) {
     return (static_cast<int64_t>(M) + 1) * U * kRowWaves * static_cast<int64_t>(sizeof(LsePart));
 }
@@ -1449,30 +1511,16 @@ bool js_launch(const void *avg, const void *workers, int32_t bf16, int32_t M, in
     const int64_t o_top = js_part_bytes(M, U), o_flag = o_top + js_top_bytes(U);
     JsWork w{reinterpret_cast<LsePart *>(ws), reinterpret_cast<u32x4 *>(ws + o_top),
              reinterpret_cast<int32_t *>(ws + o_flag)};
-    const dim3 token_waves(static_cast<unsigned>((U + kWaveTokens - 1) / kWaveTokens));
     // The wave kernel names a row thread's vectors by 16-bit indices.
     const bool wave_path =
         k <= kWaveMaxK && js_thread_vectors(K, bf16 ? JsBF16::kPer : JsF32::kPer) <= kTopIndexLimit;
     // The radix kernel takes every token, or after the wave kernel only the
     // flagged ones (few): then a few blocks per CU walk the flags.
     const dim3 tokens(static_cast<unsigned>(wave_path ? std::min<int64_t>(U, 4 * std::max(num_cus, 1)) : U));
-    if (bf16) {
-        js_launch_rows<JsBF16>(p, w, num_cus, stream);
-        if (wave_path && k <= kWaveCandSmall / 2)
-            hipLaunchKernelGGL((js_token_wave_kernel<JsBF16, kWaveCandSmall>), token_waves, dim3(kBlock), 0, stream, p, w);
-        else if (wave_path)
-            hipLaunchKernelGGL((js_token_wave_kernel<JsBF16, kWaveCandLarge>), token_waves, dim3(kBlock), 0, stream, p, w);
-        hipLaunchKernelGGL(js_token_radix_kernel<JsBF16>, tokens, dim3(kBlock), 0, stream, p, w,
-                           wave_path ? static_cast<const int32_t *>(w.flag) : nullptr);
-    } else {
-        js_launch_rows<JsF32>(p, w, num_cus, stream);
-        if (wave_path && k <= kWaveCandSmall / 2)
-            hipLaunchKernelGGL((js_token_wave_kernel<JsF32, kWaveCandSmall>), token_waves, dim3(kBlock), 0, stream, p, w);
-        else if (wave_path)
-            hipLaunchKernelGGL((js_token_wave_kernel<JsF32, kWaveCandLarge>), token_waves, dim3(kBlock), 0, stream, p, w);
-        hipLaunchKernelGGL(js_token_radix_kernel<JsF32>, tokens, dim3(kBlock), 0, stream, p, w,
-                           wave_path ? static_cast<const int32_t *>(w.flag) : nullptr);
-    }
+    if (bf16)
+        js_launch_tokens<JsBF16>(p, w, wave_path, tokens, num_cus, stream);
+    else
+        js_launch_tokens<JsF32>(p, w, wave_path, tokens, num_cus, stream);
     if (hipGetLastError() != hipSuccess) return false;
     if (mean_out) {
         hipLaunchKernelGGL(js_mean_kernel, dim3(M), dim3(256), 0, stream, d_out, U, mean_out);

@@ -1,5 +1,6 @@
 """GPU parity of the JS distance where a row's sweeps are shared by two or
-four thread groups (calls of few rows over at least 16 sweeps of a row): both
+four thread groups (calls of few rows over at least 16 sweeps of a row), and
+where a block shares one token (calls of few tokens): both
 sides of every line of that choice, ragged last sweeps, groups whose elements
 are all masked, and values on both sides of the bf16 exp table, against the
 CPU oracle with the bars of tests/test_gpu_js.py.
@@ -82,3 +83,18 @@ def test_masked_groups(env, dead, dtype):
         w[0] = a  # a worker equal to the averaged model: exactly 0
         d = _check(fgd, torch, a, w, dtype, K, 100)
         assert (d[0] == 0).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("k,per_cu", [(100, 2), (256, 2), (257, 3), (512, 3)])
+def test_tokens_at_the_lines(env, k, per_cu, dtype):
+    """Tokens at and past the count up to which a block shares one token's
+    terms, and worker counts that leave its waves without a worker or need
+    more than one turn."""
+    fgd, torch = env
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    K = 600
+    for M, U in ((1, 3), (2, 3), (4, 3), (5, 3), (9, 3), (17, 2), (3, per_cu * cus), (3, per_cu * cus + 1)):
+        print(f"[js share] {dtype} k {k} M {M} U {U}", flush=True)
+        A, W = slog.numpy_logits(M, U, K, K, dtype, seed=k + M)
+        _check(fgd, torch, A, W, dtype, K, k)
