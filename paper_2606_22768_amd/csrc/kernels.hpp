@@ -231,21 +231,33 @@ __device__ inline uint32_t pack_bf16(float a, float b) {
 template <int V>
 struct ParamBF16 {
     static constexpr int kElem = 2;
-    __device__ static void load(rsrc_t r, uint32_t off, float (&o)[V]) {
+    static constexpr int kWords = V >= 2 ? V / 2 : 1;  // 32-bit words of a lane's vector (V == 1: the low half of one)
+    __device__ static void load_words(rsrc_t r, uint32_t off, uint32_t (&w)[kWords]) {
         if constexpr (V == 8) {
             const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kLoadPolicy);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { o[2 * k] = bf16_lo(t[k]); o[2 * k + 1] = bf16_hi(t[k]); }
+            for (int k = 0; k < 4; ++k) w[k] = t[k];
         } else if constexpr (V == 4) {
             const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kLoadPolicy);
-            o[0] = bf16_lo(t[0]); o[1] = bf16_hi(t[0]); o[2] = bf16_lo(t[1]); o[3] = bf16_hi(t[1]);
+            w[0] = t[0]; w[1] = t[1];
         } else if constexpr (V == 2) {
-            const uint32_t t = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kLoadPolicy);
-            o[0] = bf16_lo(t); o[1] = bf16_hi(t);
+            w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kLoadPolicy);
         } else {
-            const uint16_t t = __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, kLoadPolicy);
-            o[0] = __uint_as_float(static_cast<uint32_t>(t) << 16);
+            w[0] = __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, kLoadPolicy);
         }
+    }
+    __device__ static void widen(const uint32_t (&w)[kWords], float (&o)[V]) {
+        if constexpr (V == 1) {
+            o[0] = bf16_lo(w[0]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) { o[2 * k] = bf16_lo(w[k]); o[2 * k + 1] = bf16_hi(w[k]); }
+        }
+    }
+    __device__ static void load(rsrc_t r, uint32_t off, float (&o)[V]) {
+        uint32_t w[kWords];
+        load_words(r, off, w);
+        widen(w, o);
     }
     __device__ static void store(rsrc_t r, uint32_t off, const float (&i)[V], float (&s)[V]) {
         if constexpr (V == 1) {
@@ -639,7 +651,28 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
     // beyond P; lanes entirely beyond P load nothing.
     float u1[MMAX][V];  // theta_prev, then Mix1 output (unless global)
     float u2[MMAX][V];  // theta_local, then g0, then Mix2 output (unless global)
-    if (FULL || nv > 0) {
+    if constexpr (!EXACT && kE == 2) {
+        // bf16 in a class's kernels: the loads are fenced off from the words'
+        // conversion to float.  The scheduler otherwise moves each conversion
+        // up to its load, in the kernels that read the kinds at run time down
+        // to one load in flight (3 workers x 16M, global Mix1 alone: 322 us
+        // so, 206 fenced; the exact kernels keep their loads together).
+        uint32_t w1[MMAX][PIO::kWords], w2[MMAX][PIO::kWords];
+        if (FULL || nv > 0) {
+#pragma unroll
+            for (int m = 0; m < MMAX; ++m) {
+                const bool live = row_live<MMAX, EXACT>(m, M);
+                PIO::load_words(row_rsrc_if(live, a.theta_prev, m * a.ld + tb, kE), off_p, w1[m]);
+                PIO::load_words(row_rsrc_if(live, a.theta_local, m * a.ld + tb, kE), off_p, w2[m]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MMAX; ++m) {
+            PIO::widen(w1[m], u1[m]);
+            PIO::widen(w2[m], u2[m]);
+        }
+    } else if (FULL || nv > 0) {
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {
             const bool live = row_live<MMAX, EXACT>(m, M);

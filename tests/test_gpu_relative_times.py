@@ -1,0 +1,78 @@
+"""Times of one call against another of the same build, in one process and in
+turn, where a dispatch or a schedule went wrong once: a call that does less of
+the same work, or the same work on rows that lie otherwise, takes no longer
+than the bound, which lies between the ratio with the fault and without it
+(both stated).  Absolute times are the benchmark's.
+"""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_2606_22768_amd as fgd
+
+    return fgd, torch
+
+
+def _times(torch, *calls, rounds=9, n=6):
+    """The least time per call (us) of each, over rounds in turn."""
+    for call in calls:
+        for _ in range(3):
+            call()
+    best = [float("inf")] * len(calls)
+    for r in range(rounds):
+        for i, call in enumerate(calls) if r % 2 == 0 else reversed(list(enumerate(calls))):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(n):
+                call()
+            b.record()
+            b.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 1e3 / n)
+    return best
+
+
+def _ring(M):
+    from synth import configs
+
+    return configs.topology(("ring", "metropolis", 0.0), M, 1, 0)
+
+
+def _engine(fgd, M, P, dtype, mix1, mix2, ld=None, with_x=False):
+    """An engine and its arrays, all zero, one after another."""
+    eng = fgd.Engine(M, P, (P + 7) // 8 * 8 if ld is None else ld, dtype)
+    for slot, kind in (("mix1", mix1), ("mix2", mix2)):
+        if kind == "ring":
+            eng.set_topology_dict(slot, _ring(M))
+        else:
+            eng.set_topology(slot, kind)
+    mem = eng.alloc_state(spread=False, with_x=with_x)
+    for k in ("theta_prev", "theta_local", "momentum") + (("x",) if with_x else ()):
+        mem[k].zero_()
+    return eng, mem
+
+
+@pytest.mark.parametrize("mix1,mix2", [("global", "identity"), ("identity", "global")])
+def test_three_workers_take_no_longer_than_four(env, mix1, mix2):
+    """bf16 steps whose kinds are read at run time.  Three workers took 1.80
+    times as long as four with one row load in flight at a time, 1.15 with
+    all of them (322 and 206 us; four workers 179)."""
+    fgd, torch = env
+    P = 16_000_000
+    runs, keep = [], []
+    for M in (3, 4):
+        eng, mem = _engine(fgd, M, P, "bf16", mix1, mix2)
+        cd = torch.zeros((eng.num_cd_rows(), M), dtype=torch.float64, device="cuda")
+        runs.append(lambda e=eng, m=mem, c=cd: e.outer_step(m["theta_prev"], m["theta_local"], m["momentum"], c))
+        keep.append(eng)
+    three, four = _times(torch, *runs)
+    print(f"[times] step {mix1} {mix2}: three workers {three:.0f} us, four {four:.0f} us", flush=True)
+    for eng in keep:
+        eng.close()
+    assert three <= 1.4 * four
