@@ -626,6 +626,20 @@ struct TileCtx {
     int M, tid, lane, n1, n2;
 };
 
+// A block's four waves meet at a tile of a class's kernels, before its loads
+// and before its stores.  Rows that are no multiple of a 128-byte line leave
+// neighbouring waves a line in common at every row, which is fetched twice
+// and written in two parts when the waves run apart, as they do without a
+// branch per row.  Blocking half, float32, us with the waves apart, together,
+// and (before the class kernels) with a branch around each row's accesses:
+// 20 workers x 20M 2895 / 2584 / 2698, 28 x 9.1M 1713 / 1529 / 1626; on rows
+// that are whole lines, 20 x 16M 1811 / 1801 / 2000.  Every wave of a block
+// takes the same full tiles.
+template <bool EXACT, bool FULL>
+__device__ __forceinline__ void waves_meet() {
+    if constexpr (!EXACT && FULL) __builtin_amdgcn_s_barrier();
+}
+
 // One tile of kBlock * V parameters.  FULL: every lane's vector lies below P
 // (uniform; all tiles but the last), so no lane needs bounds logic.
 // MS: Mix1 is also applied to the momentum rows before the update.
@@ -649,6 +663,7 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
     // ragged tile a lane whose vector straddles P still loads the whole
     // vector (the row's ld span covers it) and zeroes the elements at or
     // beyond P; lanes entirely beyond P load nothing.
+    waves_meet<EXACT, FULL>();
     float u1[MMAX][V];  // theta_prev, then Mix1 output (unless global)
     float u2[MMAX][V];  // theta_local, then g0, then Mix2 output (unless global)
     if constexpr (!EXACT && kE == 2) {
@@ -780,6 +795,7 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
         } else {
             mix_apply<MMAX, EXACT, V, K1>(a.mix1, M, vm, vbar, c.rows, c.tid, nullptr, 0, c.lane, 0u);
         }
+        waves_meet<EXACT, FULL>();
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) finish_row(m, vm[m], vm[m]);
     } else {
@@ -801,6 +817,7 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
                     }
                 }
             }
+            waves_meet<EXACT, FULL>();
 #pragma unroll
             for (int j = 0; j < G; ++j)
                 if (m0 + j < MMAX) finish_row(m0 + j, vm[j], xm[GX == 1 ? 0 : j]);
@@ -945,6 +962,7 @@ __device__ __forceinline__ void mix1_tile(const StepParams &a, const TileCtx &c,
     if (c.cd_acc) cd_accumulate_about<MMAX, EXACT, V>(u, xbar, M, c.cd_acc, c.lane);
     mix_apply<MMAX, EXACT, V, K1>(a.mix1, M, u, xbar, c.rows, c.tid, c.cd_acc ? c.cd_acc + kCdStride : nullptr,
                                   kCdStride, c.lane, 0u);
+    waves_meet<EXACT, FULL>();
     if (FULL || nv > 0) {
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {

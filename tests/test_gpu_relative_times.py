@@ -76,3 +76,22 @@ def test_three_workers_take_no_longer_than_four(env, mix1, mix2):
     for eng in keep:
         eng.close()
     assert three <= 1.4 * four
+
+
+def test_rows_off_the_cache_lines(env):
+    """float32 rows that start inside a 128-byte line against rows that do
+    not: with a block's waves apart, so that each fetches the lines they
+    share, the blocking half took 1.26 times as long, together 1.12."""
+    fgd, torch = env
+    M, P = 28, 9_123_457
+    runs, keep = [], []
+    for ld in ((P + 7) // 8 * 8, (P + 31) // 32 * 32):
+        eng, mem = _engine(fgd, M, P, "f32", "global", "ring", ld=ld, with_x=True)
+        runs.append(lambda e=eng, m=mem: e.outer_step_blocking(m["x"], m["theta_prev"], m["theta_local"],
+                                                               m["momentum"]))
+        keep.append(eng)
+    off, on = _times(torch, *runs)
+    print(f"[times] blocking half: rows off the lines {off:.0f} us, on them {on:.0f} us", flush=True)
+    for eng in keep:
+        eng.close()
+    assert off <= 1.19 * on
