@@ -869,7 +869,7 @@ fgd_status fgd_mix1(fgd_engine *e, const void *theta_prev, void *x_out, float *m
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
     if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
     int grid = 0;
-    if (fgd_status st = grid_for(e, ks.mix1, lds, p.ntiles, grid, ks.blocks_per_cu)) return st;
+    if (fgd_status st = grid_for(e, ks.mix1, lds, p.ntiles, grid, ks.mix1_blocks_per_cu)) return st;
     if (num_blocks > 0) grid = std::min(grid, num_blocks);
     p.chunk_tiles = std::max<int64_t>(1, (p.ntiles + kMix1Chunks - 1) / kMix1Chunks);
     p.nchunks = (p.ntiles + p.chunk_tiles - 1) / p.chunk_tiles;

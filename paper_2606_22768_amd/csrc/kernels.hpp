@@ -1301,8 +1301,19 @@ struct SplitSet {
     const void *blocking;
     int v;
     int cd_stride;
-    int blocks_per_cu;
+    int blocks_per_cu;       // cap on resident blocks per compute unit: the blocking half
+    int mix1_blocks_per_cu;  // the Mix1 half
 };
+
+// Mix1 blocks per compute unit.  The classes of 17 to 31 workers without a
+// table only read rows and write them: two blocks cover the latency, and more
+// contend for DRAM (float32, global mean, us with as many as fit / two / one:
+// 20 workers x 9.1M 353 / 328 / 325, 24 x 16M 634 / 599 / 596, 29 x 16M
+// 734 / 727 / 758).  A table Mix1 gathers through LDS and takes as many as
+// fit (bf16, 17 to 31 workers: 7% faster so than with two).
+constexpr int mix1_blocks_per_cu(int mmax, bool exact, int k1) {
+    return !exact && mmax > 16 && mmax <= 32 && k1 != kTable ? 2 : step_blocks_per_cu(mmax);
+}
 
 template <template <int> class PIOT, int MMAX, bool EXACT, int V>
 SplitSet make_split_set(int k1, int k2, bool subset, bool mix_state) {
@@ -1324,6 +1335,7 @@ SplitSet make_split_set(int k1, int k2, bool subset, bool mix_state) {
     ks.v = V;
     ks.cd_stride = pow2_at_least(MMAX);
     ks.blocks_per_cu = step_blocks_per_cu(MMAX);
+    ks.mix1_blocks_per_cu = mix1_blocks_per_cu(MMAX, EXACT, k1);
     return ks;
 }
 

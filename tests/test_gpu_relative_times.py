@@ -95,3 +95,17 @@ def test_rows_off_the_cache_lines(env):
     for eng in keep:
         eng.close()
     assert off <= 1.19 * on
+
+
+@pytest.mark.parametrize("M", [17, 20])
+def test_mix1_half_takes_its_best_grid(env, M):
+    """The Mix1 half's own grid against two blocks per CU: 1.12 times its
+    time with as many blocks as fit, 1.00 now (the same grid)."""
+    fgd, torch = env
+    eng, mem = _engine(fgd, M, 4_000_000, "f32", "global", "ring", with_x=True)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    own, two = _times(torch, lambda: eng.mix1(mem["theta_prev"], mem["x"]),
+                      lambda: eng.mix1(mem["theta_prev"], mem["x"], num_blocks=2 * cus))
+    print(f"[times] Mix1 half, {M} workers: {own:.0f} us, with two blocks per CU {two:.0f} us", flush=True)
+    eng.close()
+    assert own <= 1.06 * two
