@@ -218,10 +218,15 @@ int64_t tiles_of(int64_t P, int v) {
 // Resident blocks per CU of the standalone consensus kernel, a read-only
 // stream of every row.  Up to 16 workers a lane already has a load of every
 // row in flight and more blocks only add DRAM contention (8 x 1.1e9 bf16:
-// 2.69 ms with 2 blocks, 2.72 with 4, 2.89 with 8, 4.32 with 1); with more
-// workers a lane holds one parameter and the occupancy covers the latency
-// (64 x 124M f32: 5.05 ms with 8, 5.16 with 2).
-constexpr int consensus_blocks_per_cu(int num_workers) { return num_workers <= 16 ? 2 : 8; }
+// 2.69 ms with 2 blocks, 2.72 with 4, 2.89 with 8, 4.32 with 1); so up to 24
+// workers of float32 rows (us with 2 blocks / 8: 17 x 5.6M 70 / 77, 18 x 20M
+// 239 / 263, 20 x 5.6M 80 / 85, 24 x 30M 425 / 442; 28 x 5.6M 113 / 109).
+// With more workers, and from 17 on in bf16 (17 x 16M: 112 / 102), a lane
+// holds one or two parameters and the occupancy covers the latency (64 x 124M
+// f32: 5.05 ms with 8, 5.16 with 2).
+constexpr int consensus_blocks_per_cu(int num_workers, int32_t dtype) {
+    return num_workers <= (dtype == FGD_BF16 ? 16 : 24) ? 2 : 8;
+}
 
 fgd_status grid_for_cus(int num_cus, const void *kernel, size_t lds, int64_t ntiles, int &grid,
                         int cap = kMaxBlocksPerCu) {
@@ -966,7 +971,7 @@ fgd_status fgd_consensus_distance(fgd_engine *e, const void *x, int32_t dtype, d
     p.M = c.num_workers;
     p.partials = e->d_partials;
     int grid = 0;
-    if (fgd_status st = grid_for(e, ks.consensus, 0, p.ntiles, grid, consensus_blocks_per_cu(c.num_workers)))
+    if (fgd_status st = grid_for(e, ks.consensus, 0, p.ntiles, grid, consensus_blocks_per_cu(c.num_workers, dtype)))
         return st;
     if (static_cast<size_t>(grid) * c.num_workers > e->partials_capacity)
         return fail(FGD_ERR_UNSUPPORTED, "consensus scratch too small");
@@ -1002,7 +1007,8 @@ fgd_status fgd_consensus_distance_noalloc(int32_t num_workers, int64_t num_param
     p.M = num_workers;
     p.partials = partials;
     int grid = 0;
-    if (fgd_status st = grid_for_cus(num_cus, ks.consensus, 0, p.ntiles, grid, consensus_blocks_per_cu(num_workers)))
+    if (fgd_status st = grid_for_cus(num_cus, ks.consensus, 0, p.ntiles, grid,
+                                     consensus_blocks_per_cu(num_workers, dtype)))
         return st;
     // The grid of fgd_consensus_distance (so the same sums in the same
     // order), capped to the blocks the scratch holds on a larger device.
