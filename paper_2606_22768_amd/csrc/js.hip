@@ -1411,7 +1411,8 @@ void js_token_wave_kernel(JsParams a, JsWork w) {
     // Us per call, 8 lanes a worker -> this: 2 workers x 85 tokens k = 100
     // 48 -> 37 and k = 400 144 -> 98; 1 x 30 52 -> 33 and 147 -> 80.  The
     // number of lanes is a constant: at run time it cost 8 workers 2.5 us.
-    if (a.M > 4)
+    // With at most one term per lane there is no chain to share.
+    if (a.M > 4 || a.k <= kJsLanes)
         wave_js_terms<E, kJsLanes, false>(a, w, L, u, wave, lane, tab);
     else if (a.M > 2)
         wave_js_terms<E, kWave / 4, false>(a, w, L, u, wave, lane, tab);
@@ -1470,8 +1471,12 @@ void js_launch_wave(const JsParams &p, const JsWork &w, int num_cus, hipStream_t
     // 82 / 80, k = 300 134 / 118, 1024 tokens 116 / 118 and 170 / 166, 1500
     // tokens 162 / 174 and 221 / 257; 1 worker, 256 tokens 31 / 30 and
     // 60 / 58): with more, the waves that wait for the selection take the
-    // places of others' selections.
-    if (p.U <= static_cast<int64_t>(kCand == kWaveCandSmall ? 2 : 3) * std::max(num_cus, 1))
+    // places of others' selections.  With at most one term per lane (k <=
+    // kJsLanes) there is no chain to share, and a block takes fewer workers
+    // at a time than four waves do (1 token, 200 workers: k = 4 80 / 98,
+    // k = 8 80 / 90, k = 16 93 / 89, k = 24 106 / 89; 64 workers: 38 / 46,
+    // 38 / 42, 42 / 42, 47 / 42).
+    if (p.k > kJsLanes && p.U <= static_cast<int64_t>(kCand == kWaveCandSmall ? 2 : 3) * std::max(num_cus, 1))
         hipLaunchKernelGGL((js_token_wave_kernel<E, kCand, true>), dim3(static_cast<unsigned>(p.U)), dim3(kBlock), 0,
                            stream, p, w);
     else

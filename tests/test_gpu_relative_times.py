@@ -128,3 +128,17 @@ def test_consensus_of_seventeen_workers(env):
     for eng in keep:
         eng.close()
     assert a / 17 <= 1.09 * b / 16
+
+
+@pytest.mark.parametrize("M", [64, 200])
+def test_js_of_fewer_candidates(env, M):
+    """One token's distances over its top 4 take no longer than over its top
+    24: 1.10 times as long where a block shared the 4, now 0.92."""
+    fgd, torch = env
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    A = torch.randn((1, 600), device="cuda", generator=gen)
+    W = torch.randn((M, 1, 600), device="cuda", generator=gen)
+    ws = torch.empty(fgd.fgd_js_workspace_size("f32", M, 1), dtype=torch.uint8, device="cuda")
+    few, more = _times(torch, *[lambda k=k: fgd.js_distance(A, W, top_k=k, workspace=ws) for k in (4, 24)], n=40)
+    print(f"[times] JS, {M} workers: top 4 {few:.1f} us, top 24 {more:.1f} us", flush=True)
+    assert few <= 1.02 * more
