@@ -148,6 +148,17 @@ void weights_agree() {
         t.pack_tables(tab);
         check(tab.size() == static_cast<size_t>(rounds) * t.width * M * 2, "packed table size", it);
         for (size_t i = 0; i < tab.size(); i += 2) check(tab[i] >= 0 && tab[i] <= M, "packed column in range", it);
+        // The same with room for rows that do not exist: M's entries where
+        // they were in their row, (0, 0) for the rest.
+        const int stride = M + rnd(9);
+        std::vector<int32_t> wide(3, -1);
+        t.pack_tables(wide, stride);
+        check(wide.size() == static_cast<size_t>(rounds) * t.width * stride * 2, "strided table size", it);
+        for (size_t at = 0; at < wide.size(); at += 2) {
+            const size_t row = at / 2 / stride, m = at / 2 % stride;
+            const int32_t *want = m < static_cast<size_t>(M) ? &tab[2 * (row * M + m)] : nullptr;
+            check(wide[at] == (want ? want[0] : 0) && wide[at + 1] == (want ? want[1] : 0), "strided table entry", it);
+        }
     }
 }
 

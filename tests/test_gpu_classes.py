@@ -1,8 +1,9 @@
 """GPU parity of the worker classes: every worker count that is no power of
 two runs on kernels built for the top of its class, whose rows past M read 0
 and write nothing.  Both ends of every class (the fewest and the most rows
-that do not exist), against the CPU oracle with the bars of tests/_parity.py,
-and the memory around the arrays unchanged.
+that do not exist) on a few tiles, and four classes on rows so long that
+blocks take several tiles, against the CPU oracle with the bars of
+tests/_parity.py; and the memory around the arrays unchanged.
 """
 
 import pytest
@@ -41,6 +42,61 @@ def test_class_ends(env, M, dtype):
         print(f"[classes] M={M} {dtype} mix {i}", flush=True)
         pa.run_case(fgd, torch, M, 2051, dtype, s1, k1, s2, k2, seed=61 + i, mom_std=1e-3, mix1_state=state,
                     subset=subset)
+
+
+# Rows longer than every resident block takes at once: 256 blocks of 1024
+# parameters up to 16 workers, 768 of 512 (three blocks fit a CU beside their
+# LDS rows) up to 32, 768 of 256 beyond.
+LONG = [(6, 300_003), (11, 300_003), (12, 300_003), (23, 450_003), (24, 450_003), (48, 300_003), (49, 300_003)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,P", LONG)
+def test_blocks_of_several_tiles(env, M, P, dtype):
+    """Consensus sums carried from tile to tile, the rounds' LDS columns used
+    again, a subset whose segments begin and end tiles apart."""
+    fgd, torch = env
+    for i, (s1, k1, s2, k2, state, subset) in enumerate(MIXES):
+        if subset:
+            subset = [(3, 700), (5_000, 140_001), (262_150, P - 1)]
+        print(f"[classes] M={M} P={P} {dtype} mix {i}", flush=True)
+        pa.run_case(fgd, torch, M, P, dtype, s1, k1, s2, k2, seed=71 + i, mom_std=1e-3, mix1_state=state,
+                    subset=subset)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,P", LONG)
+def test_split_halves_of_several_tiles(env, M, P, dtype):
+    """The same through both halves of a split round: Mix1 blocks that take
+    several chunks, the blocking half's tile loop with and without a subset."""
+    from tests.test_gpu_split import _split_case
+
+    _split_case(env, (M, P, dtype, G, 1, ("ring", "metropolis", 0.1), 1, False, None), True)
+    _split_case(env, (M, P, dtype, ("er_mh", 0.4, 0.2), 2, ("ring_self", 0.3), 1, True,
+                      [(3, 700), (5_000, 140_001), (262_150, P - 1)]), False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,P", [(6, 600_003), (12, 600_003), (17, 600_003), (24, 1_100_003), (31, 1_100_003),
+                                 (48, 600_003)])
+def test_consensus_of_several_tiles(env, M, P, dtype):
+    """The standalone consensus kernel, up to eight blocks per CU."""
+    import numpy as np
+
+    import oracle
+    from synth import tensors
+
+    fgd, torch = env
+    ld = pa.aligned_ld(P)
+    x, _, _ = tensors.numpy_inputs(M, ld, dtype=dtype, seed=M)
+    ref = oracle.consensus(x, P=P)
+    eng = fgd.Engine(M, P, ld, dtype)
+    g = torch.from_numpy(x if dtype == "f32" else x.view(np.int16)).cuda()
+    out = torch.full((M,), float("nan"), dtype=torch.float64, device="cuda")
+    eng.consensus_distance(g if dtype == "f32" else g.view(torch.bfloat16), out)
+    torch.cuda.synchronize()
+    pa.compare_cd(out.cpu().numpy()[None, :], ref[None, :])
+    eng.close()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
