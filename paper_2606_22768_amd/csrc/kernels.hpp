@@ -1347,6 +1347,35 @@ constexpr int lanes_v_bf16(int mmax) {
     return mmax <= 8 ? FGD_V_BF16_M8 : (mmax <= 16 ? 4 : (mmax <= 32 ? 2 : 1));
 }
 
+template <template <int> class PIOT>
+constexpr int lanes_v(int mmax) {
+    return PIOT<1>::kElem == 2 ? lanes_v_bf16(mmax) : lanes_v_f32(mmax);
+}
+
+// The kernel sets of one parameter storage, for select_exact and select_class:
+// steps and consensus, steps that mix the optimizer state too, split halves.
+template <template <int> class PIOT>
+struct StepSets {
+    template <int MMAX, bool EXACT>
+    static KernelSet get(int k1, int k2, bool subset) {
+        return make_kernel_set<PIOT, MMAX, EXACT, lanes_v<PIOT>(MMAX)>(k1, k2, subset);
+    }
+};
+template <template <int> class PIOT>
+struct StateStepSets {
+    template <int MMAX, bool EXACT>
+    static KernelSet get(int k1, int k2, bool subset) {
+        return make_kernel_set_ms<PIOT, MMAX, EXACT, lanes_v<PIOT>(MMAX)>(k1, k2, subset);
+    }
+};
+template <template <int> class PIOT>
+struct SplitSets {
+    template <int MMAX, bool EXACT>
+    static SplitSet get(int k1, int k2, bool subset, bool mix_state) {
+        return make_split_set<PIOT, MMAX, EXACT, lanes_v<PIOT>(MMAX)>(k1, k2, subset, mix_state);
+    }
+};
+
 // Calls F::get<MMAX, EXACT>(args...) for the instantiation that serves M
 // workers: select_exact for M in {1, 2, 4, 8, 16, 32, 64}, select_class for
 // every other M up to 63 (see worker_class).

@@ -4,17 +4,9 @@
 
 namespace fgd {
 
-namespace {
-struct Sets {
-    template <int MMAX, bool EXACT>
-    static KernelSet get(int k1, int k2, bool subset) {
-        return make_kernel_set_ms<ParamBF16, MMAX, EXACT, lanes_v_bf16(MMAX)>(k1, k2, subset);
-    }
-};
-}  // namespace
-
 bool kernels_bf16_ms(int M, int k1, int k2, bool subset, KernelSet *out) {
-    return exact_workers(M) ? select_exact<Sets>(M, out, k1, k2, subset) : kernels_bf16_ms_class(M, k1, k2, subset, out);
+    return exact_workers(M) ? select_exact<StateStepSets<ParamBF16>>(M, out, k1, k2, subset)
+                            : kernels_bf16_ms_class(M, k1, k2, subset, out);
 }
 
 }  // namespace fgd

@@ -4,17 +4,9 @@
 
 namespace fgd {
 
-namespace {
-struct Sets {
-    template <int MMAX, bool EXACT>
-    static SplitSet get(int k1, int k2, bool subset, bool mix_state) {
-        return make_split_set<ParamBF16, MMAX, EXACT, lanes_v_bf16(MMAX)>(k1, k2, subset, mix_state);
-    }
-};
-}  // namespace
-
 bool split_kernels_bf16(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out) {
-    return exact_workers(M) ? select_exact<Sets>(M, out, k1, k2, subset, mix_state) : split_kernels_bf16_class(M, k1, k2, subset, mix_state, out);
+    return exact_workers(M) ? select_exact<SplitSets<ParamBF16>>(M, out, k1, k2, subset, mix_state)
+                            : split_kernels_bf16_class(M, k1, k2, subset, mix_state, out);
 }
 
 }  // namespace fgd

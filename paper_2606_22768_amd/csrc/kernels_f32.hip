@@ -3,17 +3,9 @@
 
 namespace fgd {
 
-namespace {
-struct Sets {
-    template <int MMAX, bool EXACT>
-    static KernelSet get(int k1, int k2, bool subset) {
-        return make_kernel_set<ParamF32, MMAX, EXACT, lanes_v_f32(MMAX)>(k1, k2, subset);
-    }
-};
-}  // namespace
-
 bool kernels_f32(int M, int k1, int k2, bool subset, KernelSet *out) {
-    return exact_workers(M) ? select_exact<Sets>(M, out, k1, k2, subset) : kernels_f32_class(M, k1, k2, subset, out);
+    return exact_workers(M) ? select_exact<StepSets<ParamF32>>(M, out, k1, k2, subset)
+                            : kernels_f32_class(M, k1, k2, subset, out);
 }
 
 }  // namespace fgd

@@ -1,20 +1,12 @@
-// The worker classes' step kernels (M no power of two) for float32 parameter storage that also apply Mix1 to the optimizer
-// state (Appendix B, GlobalM1S variants).
+// Step kernels of the worker classes (M no power of two) for float32
+// parameter storage that also apply Mix1 to the optimizer state (Appendix B,
+// GlobalM1S variants).
 #include "kernels.hpp"
 
 namespace fgd {
 
-namespace {
-struct Sets {
-    template <int MMAX, bool EXACT>
-    static KernelSet get(int k1, int k2, bool subset) {
-        return make_kernel_set_ms<ParamF32, MMAX, EXACT, lanes_v_f32(MMAX)>(k1, k2, subset);
-    }
-};
-}  // namespace
-
 bool kernels_f32_ms_class(int M, int k1, int k2, bool subset, KernelSet *out) {
-    return select_class<Sets>(M, out, k1, k2, subset);
+    return select_class<StateStepSets<ParamF32>>(M, out, k1, k2, subset);
 }
 
 }  // namespace fgd

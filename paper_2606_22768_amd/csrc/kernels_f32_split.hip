@@ -4,17 +4,9 @@
 
 namespace fgd {
 
-namespace {
-struct Sets {
-    template <int MMAX, bool EXACT>
-    static SplitSet get(int k1, int k2, bool subset, bool mix_state) {
-        return make_split_set<ParamF32, MMAX, EXACT, lanes_v_f32(MMAX)>(k1, k2, subset, mix_state);
-    }
-};
-}  // namespace
-
 bool split_kernels_f32(int M, int k1, int k2, bool subset, bool mix_state, SplitSet *out) {
-    return exact_workers(M) ? select_exact<Sets>(M, out, k1, k2, subset, mix_state) : split_kernels_f32_class(M, k1, k2, subset, mix_state, out);
+    return exact_workers(M) ? select_exact<SplitSets<ParamF32>>(M, out, k1, k2, subset, mix_state)
+                            : split_kernels_f32_class(M, k1, k2, subset, mix_state, out);
 }
 
 }  // namespace fgd
