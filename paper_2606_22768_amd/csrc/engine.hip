@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -296,6 +297,16 @@ void fill_common(const fgd_engine *e, int ring, int v, fgd::StepParams &p) {
     p.mix2 = mix_dev(e->slot[1], t2);
     p.n_seg = static_cast<int32_t>(e->subset.size() / 2);
     p.seg = seg;
+}
+
+// Whether any row of the parameter arrays or of the momentum (may be null) starts
+// inside a 128-byte line.
+bool rows_off_lines(const fgd_engine *e, std::initializer_list<const void *> params, const void *mom) {
+    constexpr uintptr_t kLine = 128;
+    const uintptr_t es = static_cast<uintptr_t>(elem_size(e->cfg.param_dtype)), ld = static_cast<uintptr_t>(e->cfg.ld);
+    uintptr_t bits = ld * es | reinterpret_cast<uintptr_t>(mom);
+    for (const void *p : params) bits |= reinterpret_cast<uintptr_t>(p);
+    return bits % kLine != 0;  // ld * es whole lines: so is ld * 4
 }
 
 // LDS rows for the table slots a kernel mixes with (use1 / use2: Mix1 / Mix2).
@@ -735,6 +746,7 @@ fgd_status fgd_outer_step(fgd_engine *e, void *theta_prev, const void *theta_loc
     const bool tables = e->slot[0].kind == 2 || e->slot[1].kind == 2;
     const bool padded = (e->slot[0].kind == 2 && e->slot[0].padded) || (e->slot[1].kind == 2 && e->slot[1].padded);
     p.lds_rows = tables ? c.num_workers + (padded ? 1 : 0) : 0;
+    p.meet = !tables && rows_off_lines(e, {theta_prev, theta_local}, momentum);
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
     if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
 
@@ -871,6 +883,7 @@ fgd_status fgd_mix1(fgd_engine *e, const void *theta_prev, void *x_out, float *m
     p.mom_out = momentum;
     p.n_cd = e->slot[0].effective_rounds() + 1;
     p.lds_rows = lds_rows_for(e, true, false);
+    p.meet = p.lds_rows == 0 && rows_off_lines(e, {theta_prev, x_out}, momentum);
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
     if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
     int grid = 0;
@@ -930,6 +943,7 @@ fgd_status fgd_outer_step_blocking(fgd_engine *e, const void *x, void *theta_pre
     p.local_out = write_local ? theta_local : nullptr;
     p.n_cd = e->slot[1].effective_rounds() + 2;
     p.lds_rows = lds_rows_for(e, false, true);
+    p.meet = rows_off_lines(e, {x, theta_prev, theta_local}, momentum);
     size_t lds = static_cast<size_t>(p.lds_rows) * fgd::kBlock * ks.v * sizeof(float);
     if (cd_out) lds += static_cast<size_t>(p.n_cd) * fgd::kWavesPerBlock * ks.cd_stride * sizeof(double);
     int grid = 0;

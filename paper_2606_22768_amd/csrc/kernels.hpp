@@ -78,7 +78,8 @@ struct StepParams {
                               // when some table pads a short row (row M is then zero)
     int32_t nesterov;         // 1: theta' = x - lr (g + mu v'); 0: theta' = x - lr v'
     float lr, mu;
-    int32_t n_seg, pad_;      // Mix2 subset: number of segments (0: Mix2 everywhere)
+    int32_t n_seg;            // Mix2 subset: number of segments (0: Mix2 everywhere)
+    int32_t meet;             // a block's waves meet at its tiles (waves_meet)
     const int64_t *seg;       // [n_seg][2] ascending half-open [begin, end) parameter ranges
     MixDev mix1, mix2;
     // Split execution (the Mix1 half and the blocking half of a round):
@@ -626,18 +627,38 @@ struct TileCtx {
     int M, tid, lane, n1, n2;
 };
 
-// A block's four waves meet at a tile of a class's kernels, before its loads
-// and before its stores.  Rows that are no multiple of a 128-byte line leave
-// neighbouring waves a line in common at every row, which is fetched twice
-// and written in two parts when the waves run apart, as they do without a
-// branch per row.  Blocking half, float32, us with the waves apart, together,
-// and (before the class kernels) with a branch around each row's accesses:
-// 20 workers x 20M 2895 / 2584 / 2698, 28 x 9.1M 1713 / 1529 / 1626; on rows
-// that are whole lines, 20 x 16M 1811 / 1801 / 2000.  Every wave of a block
-// takes the same full tiles.
-template <bool EXACT, bool FULL>
-__device__ __forceinline__ void waves_meet() {
-    if constexpr (!EXACT && FULL) __builtin_amdgcn_s_barrier();
+// A block's four waves meet at a full tile of a class's kernels, before its
+// loads and before its stores, where the caller asks for it (StepParams::meet:
+// some row starts inside a 128-byte line, and no round of a fused step or a
+// Mix1 half gathers through LDS).  Such rows leave neighbouring waves a line
+// in common at every row, which is fetched twice and written in two parts when
+// the waves run apart, as they do without a branch per row.  float32, us apart
+// / together / with a branch around each row's accesses, before the class
+// kernels: blocking half, 20 workers x 20M 2895 / 2584 / 2698, 28 x 9.1M
+// 1713 / 1529 / 1626; step, global Mix1 alone, 20 x 20M 2054 / 1834 / 1963.
+// On rows that are whole lines there is nothing to share, and where tables or
+// the state are mixed the waves had better run apart, one loading while
+// another mixes (apart / together: two table mixes 12 x 9.1M bf16 404 / 420,
+// 7 x 16M 350 / 422; state mixed 30 x 16M float32 1633 / 2030).  Every wave of
+// a block takes the same full tiles.
+template <bool MEETS, bool FULL>
+__device__ __forceinline__ void waves_meet(const StepParams &a) {
+    if constexpr (MEETS && FULL) {
+        if (a.meet) __builtin_amdgcn_s_barrier();  // uniform
+    }
+}
+// Whether a kernel's tiles can meet: in the classes where it pays on every
+// size measured (time together over apart in the classes left out, rows off
+// the lines: blocking half, 3 workers float32 0.97 to 1.01, 3 to 7 bf16 0.89
+// to 1.04; step without tables, 3 workers float32 1.00 to 1.06, 5 to 15 bf16
+// 0.87 to 1.08; Mix1 half, 3 to 7 workers 0.99 to 1.04, 9 to 15 bf16 0.93 to
+// 1.00, but 1.12 on whole lines).
+constexpr bool step_meets(int mmax, bool exact, int e, int k1, int k2, bool state) {
+    return !exact && !state &&
+           (k1 == kStored ? mmax > (e == 4 ? 4 : 8) : k1 != kTable && k2 != kTable && mmax > (e == 4 ? 4 : 16));
+}
+constexpr bool mix1_meets(int mmax, bool exact, int e, int k1) {
+    return !exact && k1 != kTable && mmax > (e == 4 ? 8 : 16);
 }
 
 // One tile of kBlock * V parameters.  FULL: every lane's vector lies below P
@@ -663,15 +684,17 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
     // ragged tile a lane whose vector straddles P still loads the whole
     // vector (the row's ld span covers it) and zeroes the elements at or
     // beyond P; lanes entirely beyond P load nothing.
-    waves_meet<EXACT, FULL>();
+    constexpr bool kMeets = step_meets(MMAX, EXACT, kE, K1, K2, MS);
+    waves_meet<kMeets, FULL>(a);
     float u1[MMAX][V];  // theta_prev, then Mix1 output (unless global)
     float u2[MMAX][V];  // theta_local, then g0, then Mix2 output (unless global)
-    if constexpr (!EXACT && kE == 2) {
-        // bf16 in a class's kernels: the loads are fenced off from the words'
-        // conversion to float.  The scheduler otherwise moves each conversion
-        // up to its load, in the kernels that read the kinds at run time down
-        // to one load in flight (3 workers x 16M, global Mix1 alone: 322 us
-        // so, 206 fenced; the exact kernels keep their loads together).
+    if constexpr (!EXACT && MMAX == 4 && kE == 2 && K1 == kAny) {
+        // 3 workers in bf16 on the kernel that reads the kinds at run time:
+        // the loads are fenced off from the words' conversion to float, which
+        // the scheduler otherwise moves up between them, down to one load in
+        // flight (16M parameters, global Mix1 alone: 322 us so, 193 fenced).
+        // The other kernels keep their loads together or lose by the fence
+        // (56 workers x 4M: 558 us without it, 915 with it).
         uint32_t w1[MMAX][PIO::kWords], w2[MMAX][PIO::kWords];
         if (FULL || nv > 0) {
 #pragma unroll
@@ -795,7 +818,6 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
         } else {
             mix_apply<MMAX, EXACT, V, K1>(a.mix1, M, vm, vbar, c.rows, c.tid, nullptr, 0, c.lane, 0u);
         }
-        waves_meet<EXACT, FULL>();
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) finish_row(m, vm[m], vm[m]);
     } else {
@@ -817,7 +839,7 @@ __device__ __forceinline__ void step_tile(const StepParams &a, const TileCtx &c,
                     }
                 }
             }
-            waves_meet<EXACT, FULL>();
+            waves_meet<kMeets, FULL>(a);
 #pragma unroll
             for (int j = 0; j < G; ++j)
                 if (m0 + j < MMAX) finish_row(m0 + j, vm[j], xm[GX == 1 ? 0 : j]);
@@ -962,7 +984,7 @@ __device__ __forceinline__ void mix1_tile(const StepParams &a, const TileCtx &c,
     if (c.cd_acc) cd_accumulate_about<MMAX, EXACT, V>(u, xbar, M, c.cd_acc, c.lane);
     mix_apply<MMAX, EXACT, V, K1>(a.mix1, M, u, xbar, c.rows, c.tid, c.cd_acc ? c.cd_acc + kCdStride : nullptr,
                                   kCdStride, c.lane, 0u);
-    waves_meet<EXACT, FULL>();
+    waves_meet<mix1_meets(MMAX, EXACT, kE, K1), FULL>(a);
     if (FULL || nv > 0) {
 #pragma unroll
         for (int m = 0; m < MMAX; ++m) {

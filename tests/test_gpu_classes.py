@@ -77,6 +77,22 @@ def test_split_halves_of_several_tiles(env, M, P, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,P", [(M, P) for M in (3, 6, 11, 24, 49) for P in (2051, 2112)] + LONG[::2])
+def test_steps_without_tables(env, M, P, dtype):
+    """No round gathers through LDS; rows that start inside a 128-byte line
+    and (P = 2112) rows that are whole lines, which decides whether a block's
+    waves meet at its tiles.  Both halves too."""
+    from tests.test_gpu_split import _split_case
+
+    fgd, torch = env
+    for i, (s1, k1, s2, k2, state) in enumerate([(G, 1, ID, 0, False), (ID, 0, G, 1, False), (G, 1, ID, 0, True)]):
+        print(f"[classes] M={M} P={P} {dtype} mix {i}", flush=True)
+        pa.run_case(fgd, torch, M, P, dtype, s1, k1, s2, k2, seed=81 + i, mom_std=1e-3, mix1_state=state)
+    _split_case(env, (M, P, dtype, G, 1, ID, 0, False, None), True)
+    _split_case(env, (M, P, dtype, ID, 0, ("ring", "metropolis", 0.1), 1, False, None), False)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("M,P", [(6, 600_003), (12, 600_003), (17, 600_003), (24, 1_100_003), (31, 1_100_003),
                                  (48, 600_003)])
 def test_consensus_of_several_tiles(env, M, P, dtype):

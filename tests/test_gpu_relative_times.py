@@ -61,8 +61,8 @@ def _engine(fgd, M, P, dtype, mix1, mix2, ld=None, with_x=False):
 @pytest.mark.parametrize("mix1,mix2", [("global", "identity"), ("identity", "global")])
 def test_three_workers_take_no_longer_than_four(env, mix1, mix2):
     """bf16 steps whose kinds are read at run time.  Three workers took 1.80
-    times as long as four with one row load in flight at a time, 1.15 with
-    all of them (322 and 206 us; four workers 179)."""
+    times as long as four with one row load in flight at a time, 1.08 with
+    all of them (322 and 193 us; four workers 179)."""
     fgd, torch = env
     P = 16_000_000
     runs, keep = [], []
