@@ -1473,10 +1473,17 @@ void js_launch_wave(const JsParams &p, const JsWork &w, int num_cus, hipStream_t
     // 60 / 58): with more, the waves that wait for the selection take the
     // places of others' selections.  With at most one term per lane (k <=
     // kJsLanes) there is no chain to share, and a block takes fewer workers
-    // at a time than four waves do (1 token, 200 workers: k = 4 80 / 98,
-    // k = 8 80 / 90, k = 16 93 / 89, k = 24 106 / 89; 64 workers: 38 / 46,
-    // 38 / 42, 42 / 42, 47 / 42).
-    if (p.k > kJsLanes && p.U <= static_cast<int64_t>(kCand == kWaveCandSmall ? 2 : 3) * std::max(num_cus, 1))
+    // at a time than four waves do (1 token, 200 workers, a wave / a block:
+    // k = 4 80 / 98, k = 8 80 / 90, k = 16 93 / 89, k = 24 106 / 89; 64
+    // workers: 38 / 46, 38 / 42, 42 / 42, 47 / 42); the block then pays where
+    // a wave per token leaves most CUs without a block, or for two workers
+    // at most (block over wave, k = 1 to 8, 1 to 200 workers: 3 to 64 tokens
+    // 0.91 to 1.17, of 1 and 2 workers 0.94 to 1.00; 100 to 256 tokens 0.85 to
+    // 1.01; 300 and 384 tokens 0.96 to 1.04).
+    const int64_t cus = std::max(num_cus, 1);
+    const bool share = p.k > kJsLanes ? p.U <= (kCand == kWaveCandSmall ? 2 : 3) * cus
+                                      : p.U <= cus && (p.M <= 2 || 3 * p.U > cus);
+    if (share)
         hipLaunchKernelGGL((js_token_wave_kernel<E, kCand, true>), dim3(static_cast<unsigned>(p.U)), dim3(kBlock), 0,
                            stream, p, w);
     else

@@ -182,10 +182,13 @@ def test_tokens_of_one_wave(env, k, K, per_cu, dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("k", [7, 8, 9, 16, 17])
 def test_few_candidates(env, k, dtype):
-    """At most 8 candidates take a wave per token and 8 lanes per worker
-    however few the tokens and workers, more a block per token."""
+    """At most 8 candidates take a wave per token and 8 lanes per worker, but
+    a block per token with two workers at most or from a third of a token per
+    CU on up to one; more candidates a block per token."""
     fgd, torch = env
-    for M in (1, 2, 4, 5, 9, 17):
-        print(f"[js few] {dtype} k {k} M {M}", flush=True)
-        A, W = slog.numpy_logits(M, 3, 600, 600, dtype, seed=k + M)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for M, U in ((1, 3), (2, 3), (3, 3), (4, 3), (5, 3), (9, 3), (17, 3), (3, cus // 3), (9, cus // 3 + 1),
+                 (5, cus), (2, cus), (2, cus + 1), (3, cus + 1)):
+        print(f"[js few] {dtype} k {k} M {M} U {U}", flush=True)
+        A, W = slog.numpy_logits(M, U, 600, 600, dtype, seed=k + M)
         _check(fgd, torch, A, W, dtype, 600, k)
