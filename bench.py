@@ -181,7 +181,7 @@ def js_bench(args, fgd, torch):
            "kernel_source_hash": lib_hash["js"], "library_source_hash": lib_hash}
     out["pattern_reference"] = {"ms": round(pat_ms, 4), "gbs": round(nbytes / (pat_ms * 1e-3) / 1e9, 1),
                                 "call_rate_vs_pattern": round(pat_ms / avg, 4),
-                                "what": "the row kernel's loads (same grid, rows, lanes, cache hints, prefetch) "
+                                "what": "js_rows_kernel's loads (same grid, rows, lanes, cache hints, prefetch) "
                                         "without its arithmetic; the call adds the per-token kernels"}
     out["copy_reference_gbs"] = copy_reference(fgd, torch, A.device, args.copy_gb)
     if not args.no_cpu_baseline:

@@ -387,8 +387,13 @@ fgd_status fgd_read_timing(fgd_engine *e, double *total_ms, int64_t *count);
  *                   carries each row's log-sum-exp parts and the averaged
  *                   rows' largest vector maxima per thread from the call's
  *                   first kernel to the next)
- * Enqueued on `stream`; deterministic.  Calls that share a workspace must
- * not run concurrently. */
+ * Enqueued on `stream`; deterministic: equal calls (M, U, K, top_k, dtype) on
+ * one device give equal bits.  The order of a token's sums depends on those
+ * sizes and on the device's number of compute units, so the same token in a
+ * call of other sizes (another batch, other workers beside it) may differ in
+ * the last bits of d; T(u) may not, and a worker whose logits equal the
+ * averaged model's has d = 0 in every call.  Calls that share a workspace
+ * must not run concurrently. */
 fgd_status fgd_js_distance(const void *logits_avg, const void *logits_workers, int32_t dtype, int32_t num_workers,
                            int64_t num_tokens, int64_t vocab, int64_t ldk, int32_t top_k, double *d_out,
                            double *mean_out, int32_t *topk_out, void *workspace, int64_t workspace_bytes,
@@ -416,7 +421,10 @@ fgd_status fgd_stream_step_pattern(fgd_engine *e, void *theta_prev, const void *
 /* Streaming reference for fgd_js_distance: the loads of its row kernel (the
  * same grid, rows, lane elements, cache hints and prefetch) and none of its
  * arithmetic; the logits are only read, and the workspace is left undefined.
- * Its rate is the practical ceiling of that kernel's access pattern.  Same
+ * Its rate is the practical ceiling of that kernel's access pattern, for
+ * calls that run it: those of more than three rows ((M + 1) U) per compute
+ * unit, or of rows of at most 60 KB (fewer rows that are longer are streamed
+ * by several thread groups each, which this does not follow).  Same
  * logits, sizes and workspace rules as fgd_js_distance.  Enqueued on
  * `stream`. */
 fgd_status fgd_stream_js_pattern(const void *logits_avg, const void *logits_workers, int32_t dtype,

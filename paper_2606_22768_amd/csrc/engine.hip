@@ -519,7 +519,8 @@ fgd_status fgd_create(const fgd_config *cfg, fgd_engine **out) {
             return hip_fail(err, "querying the compute-unit count");
         }
         const size_t M = static_cast<size_t>(cfg->num_workers);
-        // Largest packed tables (both slots, FGD_MAX_ROUNDS rounds, width M),
+        // Largest packed tables (both slots, FGD_MAX_ROUNDS rounds, width M,
+        // worker_class(M) rows),
         // then the largest subset.
         e->topo_capacity = subset_offset(2 * static_cast<size_t>(FGD_MAX_ROUNDS) * M *
                                          fgd::worker_class(cfg->num_workers) * 2 * sizeof(int32_t)) +

@@ -15,16 +15,18 @@
 // Probabilities are those of the full softmax; only the sum is restricted to
 // T.  Kernels, in order on the call's stream, with a caller workspace between
 // them:
-//   js_rows_kernel         (few rows: js_rows_split_kernel, a row per block)
-//                          streams all (M + 1) U rows once (persistent, no
+//   js_rows_kernel         streams all (M + 1) U rows once (persistent, no
 //                          barriers): per row, each wave's (shift, sum) part
 //                          of the log-sum-exp; per averaged row, each row
-//                          thread's four largest vector maxima (key, index)
+//                          thread's four largest vector maxima (key, index).
+//                          Few rows: js_rows_split_kernel, a row per block,
+//                          its sweeps shared by two or four thread groups
 //   js_token_wave_kernel   (k <= 512) one wave per token: the averaged row's
 //                          lse from its parts, the selection (a threshold from
 //                          the recorded maxima, a second read of only the
-//                          vectors that reach it), the JS terms; a token with
-//                          too many candidates is flagged
+//                          vectors that reach it), the JS terms, which with
+//                          few tokens the block's other waves share; a token
+//                          with too many candidates is flagged
 //   js_token_radix_kernel  per token, a radix select over the whole row: every
 //                          token when k > 512, else only the flagged ones
 //   js_mean_kernel         the per-worker mean of d
@@ -55,9 +57,12 @@
 // adding n << 12 leaves the mantissa alone and adds n >> 8 to the
 // exponent); x is clamped at -708 so that the scaled entry stays a normal
 // double.  Lanes, then a row's waves, are combined through the largest
-// shift (one exp per part, no pairwise rescaling).  Every reduction has a
-// fixed order, so results are deterministic.  The selected indices are
-// rank-sorted so that the JS sum runs in index order.
+// shift (one exp per part, no pairwise rescaling).  Every reduction has an
+// order that the call's sizes, its dtype and the device's compute-unit count
+// fix, so equal calls give equal bits; a token in a call of other sizes may
+// differ in its last bits (another number of groups per row or of lanes per
+// worker).  The selected indices are rank-sorted so that a lane's JS terms run
+// in index order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -726,8 +731,16 @@ void js_rows_kernel(JsParams a, JsWork w) {
 // js_rows_kernel's, with the same maxima, and an averaged row and a worker
 // row still run the same sums.  The row's first load is in flight while the
 // tables are filled.  js_launch_rows has the times and the choice.
-constexpr int64_t kSplitMinSweeps = 16;  // below it the merge costs what a shorter chain gains (5 sweeps, 600 rows:
-                                         // 37.3 us a call with one group a row, 37.7 with two, 41.8 with four)
+// The fewest sweeps a row is split from.  Us per call over one / two / four
+// groups a row, 252 rows (4 groups are the choice) and 750 (2): float32, 4
+// sweeps 26.7 / 25.8 / 26.8 and 27.0 / 26.6 / 29.4, 8 sweeps 28.4 / 27.1 / 27.5
+// and 29.7 / 28.4 / 30.5, 12 sweeps 30.8 / 28.6 / 28.7 and 32.7 / 30.9 / 32.7,
+// 16 sweeps 32.5 / 29.4 / 29.4 and 35.1 / 32.9 / 34.4; bf16, 4 sweeps
+// 29.5 / 28.6 / 29.0 and 31.3 / 32.3 / 34.6, 8 sweeps 32.2 / 29.9 / 29.9 and
+// 33.4 / 33.5 / 35.7, 12 sweeps 34.5 / 31.2 / 30.7 and 36.2 / 35.8 / 37.6, 16
+// sweeps 35.8 / 32.0 / 31.3 and 38.6 / 37.6 / 39.5.  So at 16 both choices pay
+// in both dtypes; up to a row per CU they do from 7 sweeps on.
+constexpr int64_t kSplitMinSweeps = 16;
 template <class E, int kSplit>
 __global__ __launch_bounds__(kRowThreads * kSplit) __attribute__((amdgpu_waves_per_eu(kSplit == 2 ? 6 : 4, 8)))
 void js_rows_split_kernel(JsParams a, JsWork w) {
@@ -1016,11 +1029,12 @@ void js_token_radix_kernel(JsParams a, JsWork w, const int32_t *flag) {
     }
 }
 
-// The row kernel's loads without its arithmetic: the same grid, row groups,
+// js_rows_kernel's loads without its arithmetic: the same grid, row groups,
 // streaming order, lane elements and prefetch, and no LDS table; each wave
 // folds what it loads into one word (an XOR) and stores it over its part in
 // the workspace, so no load can be dropped.  Its rate is the practical
-// ceiling of the row kernel's access pattern.
+// ceiling of that kernel's access pattern (calls of few rows run
+// js_rows_split_kernel, whose rows are laid out otherwise).
 template <class E>
 __global__ __launch_bounds__(kRowsBlock) void js_rows_pattern_kernel(JsParams a, JsWork w) {
     const int lt = threadIdx.x % kRowThreads;
@@ -1058,7 +1072,7 @@ __global__ __launch_bounds__(kRowsBlock) void js_rows_pattern_kernel(JsParams a,
     }
 }
 
-// ------------------------------------------------- per token, one wave each
+// ------------------------------------ per token, selected by one wave each
 constexpr int kWaveTokens = kBlock / kWave;            // tokens per block of js_token_wave_kernel
 constexpr int kRtPerLane = kRowThreads / kWave;        // row threads whose recorded maxima a lane takes
 constexpr int kRecords = kRowThreads * kTopVecs;       // recorded vector maxima per token
@@ -1348,8 +1362,8 @@ __device__ __forceinline__ bool wave_select(const JsParams &a, const JsWork &w, 
     return true;
 }
 
-// Per token, one wave (token u = blockIdx.x * kWaveTokens + wave; no block
-// barriers after the exp table): the averaged row's log-sum-exp from its
+// Per token, one wave (token u = blockIdx.x * kWaveTokens + wave; without
+// kShare no block barriers after the exp table): the averaged row's log-sum-exp from its
 // wave parts; T0, the k-th largest of the 1024 recorded vector maxima (16-bit
 // keys, built from the top bit down by counting with ballots), which is at
 // most the row's k-th largest key, so the selected tokens are among the

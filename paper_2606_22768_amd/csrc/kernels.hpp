@@ -13,9 +13,11 @@
 //            in its own column of an LDS array [M][block][V] (plus a zero
 //            row M when some table pads a short row) and gathers from there
 //            (no barrier: a lane touches only its own column).
-//            Per round the host supplies a padded table [width][M] of
-//            (column, weight): the d-th live entry of every row, in ascending
-//            column order, so the sum runs in the CSR row's order.
+//            Per round the host supplies a padded table [width][MMAX] of
+//            (column, weight), MMAX the kernel's worker bound (worker_class):
+//            the d-th live entry of every row, in ascending column order, so
+//            the sum runs in the CSR row's order; (0, 0) for the rows from M
+//            to MMAX.
 //   phase D  load momentum rows, v' = mu v + g, theta' = x - lr (g + mu v')
 //            (plain momentum: theta' = x - lr v'), store theta' (RNE to bf16
 //            for bf16 storage) and v'.  With the optimizer state mixed
@@ -60,7 +62,7 @@ struct MixDev {
     int32_t rounds;     // table rounds (kTable)
     int32_t width;      // entries per row in each round's table
     int32_t pad_;
-    const int2 *table;  // [rounds][width][M] of (column, bit pattern of float weight)
+    const int2 *table;  // [rounds][width][worker_class(M)] of (column, bit pattern of float weight)
 };
 
 struct StepParams {
@@ -108,10 +110,13 @@ constexpr int ilog2(int m) { return m <= 1 ? 0 : 1 + ilog2(m / 2); }
 // their loads return 0 and their stores write nothing, neither moving a byte
 // nor branching.  (With a branch around each row's load the loads of a tile
 // are not issued together, and the next power of two has up to half its rows
-// dead: the step at 12 workers x 7M bf16 took 596 us so and 303 with classes,
-// at 24 workers 1257 and 693 us; the consensus of 24 x 40M bf16 857 and 384.)
+// dead.  Step, global Mix1 and a ring, us so and with classes: 12 workers x 4M
+// bf16 323 and 167, float32 282 and 212; 24 x 2M 358 and 183, 283 and 220;
+// 48 x 1M 604 and 196, 441 and 237.  Over both ends of every class, all mixes
+// and both storages the ratio is 0.21 to 0.98 at these sizes.)
 // The classes are close together, so that at most a fifth of the rows is
-// dead from 9 workers on.
+// dead from 9 workers on: at 33, 41, 49 and 57 workers, the most dead rows,
+// the ratio is 0.30 to 0.53 where it is 0.29 to 0.60 at 40, 48, 56 and 63.
 constexpr int worker_class(int m) {
     return m <= 2 ? m
            : m <= 16 ? (m + 1) / 2 * 2
@@ -1246,16 +1251,25 @@ struct KernelSet {
 // 16-byte (8-byte bf16) accesses per tile, all issued before first use, which
 // keeps enough bytes in flight with one block per CU; more resident blocks
 // only add DRAM contention (measured 5-7% slower with 4 at 8 workers).  With
-// 32 or 64 workers a lane holds one or two parameters and the rows are
+// 17 to 64 workers a lane holds one or two parameters and the rows are
 // gathered through LDS, so a second block is needed to cover that latency.
+// The line up to 16 is that of large arrays.  Where arrays lie in the caches
+// and with two table mixes one block is not the fastest (us with 1 / 2 / 4
+// blocks, global Mix1 and a ring in float32: 4 x 1M 24.7 / 23.2 / 20.6,
+// 8 x 1M 46 / 42 / 43, 4 x 20M 324 / 351 / 362; two rings in bf16: 12 x 1M
+// 58 / 44 / 42, 12 x 20M 892 / 765 / 786, 8 x 20M 527 / 558 / 544).
 constexpr int step_blocks_per_cu(int mmax) { return mmax <= 16 ? FGD_STEP_BLOCKS_PER_CU_SMALL : 8; }
 
 // Kernel set of one instantiation; the step kernel is specialised on the
 // (Mix1, Mix2) kinds of the paper's configurations (Appendix A table:
-// GlobalM1LocalM2, LocalM1M2, GlobalM1, DiLoCo) when M is exact.  `subset`:
-// a Mix2 subset is set; only GlobalM1LocalM2 has a specialisation for it
-// (the paper's subset configuration), the rest run on the run-time-kind
-// kernel, which always handles subsets.
+// GlobalM1LocalM2, LocalM1M2, GlobalM1, DiLoCo) when M is exact, in the
+// classes on the first two, the configurations that gossip.  `subset`: a Mix2
+// subset is set; only GlobalM1LocalM2 has a specialisation for it (the
+// paper's subset configuration) and only when M is exact; the rest run on the
+// run-time-kind kernel, which always handles subsets.  A kernel more per
+// class is 30 more in the library; per row, 15 workers on the run-time kinds
+// take 0.98 to 1.01 times 16 on their own GlobalM1 or DiLoCo kernel, 7 and 31
+// in bf16 0.93 to 1.17 times 8 and 32, and with a subset 1.01 to 1.37 times.
 template <template <int> class PIOT, int MMAX, bool EXACT, int V>
 KernelSet make_kernel_set(int k1, int k2, bool subset) {
     using P = PIOT<V>;
@@ -1289,7 +1303,8 @@ KernelSet make_kernel_set(int k1, int k2, bool subset) {
 
 // The same with the optimizer state mixed by Mix1 (Appendix B: GlobalM1S,
 // GlobalM1SLocalM2 and GlobalM1SLocalM2-subset are specialised when M is
-// exact).
+// exact; the classes read the kinds at run time: per row, 7, 15 and 31 workers
+// take 0.97 to 1.42 times the time of 8, 16 and 32).
 template <template <int> class PIOT, int MMAX, bool EXACT, int V>
 KernelSet make_kernel_set_ms(int k1, int k2, bool subset) {
     using P = PIOT<V>;
@@ -1315,9 +1330,9 @@ KernelSet make_kernel_set_ms(int k1, int k2, bool subset) {
     return ks;
 }
 
-// Split-execution kernels of one instantiation: the Mix1 half (global mean
-// specialised when M is exact, run-time kinds otherwise) and the blocking
-// half (CSR Mix2 specialised when M is exact, with and without a subset).
+// Split-execution kernels of one instantiation: the Mix1 half (specialised on
+// the global mean; with the state mixed when M is exact) and the blocking half
+// (specialised on a CSR Mix2; with a subset when M is exact).
 struct SplitSet {
     const void *mix1;
     const void *blocking;
