@@ -636,10 +636,12 @@ struct TileCtx {
 // loads and before its stores, where the caller asks for it (StepParams::meet:
 // some row starts inside a 128-byte line, and no round of a fused step or a
 // Mix1 half gathers through LDS).  Such rows leave neighbouring waves a line
-// in common at every row, which is fetched twice and written in two parts when
-// the waves run apart, as they do without a branch per row.  float32, us apart
-// / together / with a branch around each row's accesses, before the class
-// kernels: blocking half, 20 workers x 20M 2895 / 2584 / 2698, 28 x 9.1M
+// in common at every row, which is fetched twice when the waves run apart, as
+// they do without a branch per row.  Blocking half, 28 workers x 9.1M float32:
+// 4745 MB fetched apart, 4355 together, of 4087 (the rest is the lines that two
+// tiles share); the writes gain nothing (3101 and 3158 MB of 3065).  float32,
+// us apart / together / with a branch around each row's accesses, before the
+// class kernels: blocking half, 20 workers x 20M 2895 / 2584 / 2698, 28 x 9.1M
 // 1713 / 1529 / 1626; step, global Mix1 alone, 20 x 20M 2054 / 1834 / 1963.
 // On rows that are whole lines there is nothing to share, and where tables or
 // the state are mixed the waves had better run apart, one loading while
